@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+import moe_inputs as mi
 from gpu_util import dev
 
 pytestmark = pytest.mark.gpu
@@ -87,3 +88,36 @@ def test_pack_full_size_sampled_rows(orc, name):
             s, q, s16, z16 = orc.quantize(w[rows], b, inp.cfg.group)
             assert np.array_equal(codes[rows], orc.pack(q, b))
             assert np.array_equal(sz[rows], orc.sz_words(s16, z16))
+
+
+@pytest.mark.parametrize("bits,group", [(2, 64), (4, 64), (8, 64), (3, 128), (6, 128), (8, 128), (16, 64)])
+@pytest.mark.parametrize("R,K", [(1, 128), (17, 2048), (33, 2176)])
+def test_pack_tile_edges_and_ties(orc, bits, group, R, K):
+    """Row and column remainders of the pack tile (16 rows x 2048 columns), a
+    matrix whose rows start off 16-byte alignment, and weights whose quotient
+    by the scale is exactly a half integer or within a few ulp of one, where
+    the code depends on the exact quotient."""
+    import paper_2503_21135_amd as P
+    rng = np.random.default_rng([bits, group, R, K])
+    qmax = (1 << min(bits, 8)) - 1
+    half = (rng.integers(0, qmax, (R, K)) + 0.5).astype(np.float32) * np.float32(2.0 ** -7)
+    off = rng.integers(-2, 3, (R, K))
+    w = np.where(off < 0, np.nextafter(half, np.float32(0)), np.where(off > 0, np.nextafter(half, np.float32(9)), half))
+    w[:, ::group] = 0.0                                # every group spans [0, qmax] steps of 2^-7
+    w[:, 1::group] = np.float32(qmax * 2.0 ** -7)
+    buf = torch.zeros(R * (K + 5) + 3, dtype=torch.float32, device=dev())
+    wt = buf[3:].view(R, K + 5)[:, 1:K + 1]
+    wt.copy_(torch.from_numpy(w))
+    codes = torch.zeros(R * K * bits // 32, dtype=torch.int32, device=dev())
+    sz = torch.zeros(R * (K // group), dtype=torch.int32, device=dev())
+    P.moe_quant_pack(wt, bits, group, codes, sz, ld_codes=K * bits // 32, sz_row_stride=1, sz_group_stride=R)
+    codes = codes.cpu().numpy().view(np.uint32).reshape(R, -1)
+    sz = sz.cpu().numpy().view(np.uint32).reshape(K // group, R).T
+    if bits == 16:
+        bf = mi.bf16_bits(w).astype(np.uint32)
+        assert np.array_equal(codes, bf[:, 0::2] | (bf[:, 1::2] << 16)) and np.all(sz == 0x3C00)
+        return
+    s, q, s16, z16 = orc.quantize(w, bits, group)
+    assert s == 0
+    assert np.array_equal(codes, orc.pack(q, bits))
+    assert np.array_equal(sz, orc.sz_words(s16, z16))
