@@ -1056,7 +1056,7 @@ def main():
     hbm_bound = byt["gate_up"] / HBM_PEAK_GBS >= flops_gate_up(layer, offsets) / 1e3 / BF16_PEAK_TFLOPS
     kernel = ("FFN gate/up stage (gate+up projections, SiLU-GLU epilogue): ffn_stream_kernel "
               "for up to 28 tokens per expert (48 for experts narrower than d_ff 4096; shared "
-              "experts up to 512 tokens), else tile_plan_kernel + ffn_tile_kernel; routed and "
+              "experts up to 512 tokens), else tile_prep_kernel + ffn_tile_kernel; routed and "
               "shared experts in one launch per kernel")
     if hbm_bound:
         roof = {"bound": "hbm", "kernel": kernel, "achieved": round(achieved_gbs, 1),

@@ -121,7 +121,7 @@ Plan make_plan(const moe_layer_t* L, int T, int k) {
   p.xsum_bytes = align256(sizeof(float) * static_cast<size_t>(rows) * (L->d_model / g));
   p.h_bytes = align256(sizeof(uint16_t) * static_cast<size_t>(hcols));
   p.hsum_bytes = align256(sizeof(float) * static_cast<size_t>(rows) * (fmax / g));
-  p.tile_bytes = align256(sizeof(int32_t) * 4 * (MOE_MAX_EXPERTS + 1));
+  p.tile_bytes = align256(sizeof(int32_t) * 2 * kTilePlanInts);
   const bool tiled = p.nt_routed == 0 || (S > 0 && p.nt_shared == 0);
   p.x16_bytes = tiled ? align256(sizeof(uint16_t) * static_cast<size_t>(T) * L->d_model) : 0;
   p.total = p.xsum_bytes + p.h_bytes + p.hsum_bytes + p.tile_bytes + p.x16_bytes + 256;
@@ -267,51 +267,35 @@ void launch_all(const FfnArgs& a, const Plan& p, const moe_layer_t* L, int T, hi
   const int S = a.S;
   auto event = [&](int i) -> hipEvent_t { return (ev && i < n_ev) ? ev[i] : nullptr; };
   std::vector<Launch> xsum, gate_up, hsum, down;
-  // activation preparation per row range: group sums [d/g][rows] for the
-  // streaming kernel, fp16 copies for the tile kernel
-  bool x16_done = false;
-  auto prep = [&](int p0, int p1, bool tiled) {
-    if (p1 <= p0) return;
-    if (tiled) {   // one fp16 copy of the T token rows serves every tiled range
-      if (x16_done) return;
-      x16_done = true;
-      const int64_t n = static_cast<int64_t>(T) * (a.d / 8);
-      xsum.push_back([=, &a](hipEvent_t e0, hipEvent_t e1) {
-        klaunch(gather_f16_kernel, dim3(static_cast<unsigned>(cdiv(n, 256))), dim3(256), s, e0, e1, a, T);
-      });
-    } else {
-      const int64_t n = static_cast<int64_t>(p1 - p0) * (a.d / g) * (g / 8);
-      xsum.push_back([=, &a](hipEvent_t e0, hipEvent_t e1) {
-        klaunch(group_sum_kernel<NM>, dim3(static_cast<unsigned>(cdiv(n, 256))), dim3(256), s, e0, e1,
-                a, a.x, a.perm, static_cast<int64_t>(a.d), p0, p1, a.d, p1, a.d, const_cast<float*>(a.xsum));
-      });
-    }
-  };
-  if (p.nt_routed != 0 && (S == 0 || p.nt_shared != 0)) {
-    prep(0, a.rows, false);   // every row streams: one launch of group sums
-  } else {
-    prep(0, a.Tk, p.nt_routed == 0);
-    if (S > 0) prep(a.Tk, a.rows, p.nt_shared == 0);
-  }
-  int32_t* prefix = a.tile_prefix;
-  // tile path: plan kernel, then the persistent tile kernel, over the experts
-  // that take it -- routed, shared, or both in one launch (routed first), so
-  // that one persistent grid balances all of their items
+  // the experts that take the tile kernel -- routed, shared, or both in one
+  // launch (routed first), so that one persistent grid balances all their items
   const bool tile_r = p.nt_routed == 0, tile_s = S > 0 && p.nt_shared == 0;
+  const int te0 = tile_r ? 0 : a.E, tn = (tile_r ? a.E : 0) + (tile_s ? S : 0);
+  if (tn > 0) {   // the fp16 copy of the token rows and both stages' plans, one launch
+    const TileMap m = tile_map(L, te0, tn, p.n_split);
+    const unsigned nb = static_cast<unsigned>(cdiv(static_cast<int64_t>(T) * (a.d / 8), 256)) + 1;
+    xsum.push_back([=, &a](hipEvent_t e0, hipEvent_t e1) {
+      klaunch(tile_prep_kernel, dim3(nb), dim3(256), s, e0, e1, a, m, T, a.tile_plan);
+    });
+  }
+  // group sums [d/g][rows] of the rows that stream
+  auto prep = [&](int p0, int p1) {
+    if (p1 <= p0) return;
+    const int64_t n = static_cast<int64_t>(p1 - p0) * (a.d / g) * (g / 8);
+    xsum.push_back([=, &a](hipEvent_t e0, hipEvent_t e1) {
+      klaunch(group_sum_kernel<NM>, dim3(static_cast<unsigned>(cdiv(n, 256))), dim3(256), s, e0, e1,
+              a, a.x, a.perm, static_cast<int64_t>(a.d), p0, p1, a.d, p1, a.d, const_cast<float*>(a.xsum));
+    });
+  };
+  if (!(tile_r && (tile_s || S == 0))) prep(tile_r ? a.Tk : 0, tile_s ? a.Tk : a.rows);
   auto add_tile = [&](std::vector<Launch>& v, auto nk) {
     constexpr int NK = decltype(nk)::value;
-    if (!tile_r && !tile_s) return;
-    const int e0 = tile_r ? 0 : a.E, n_e = (tile_r ? a.E : 0) + (tile_s ? S : 0);
-    const TileMap m = tile_map(L, e0, n_e, NK == 1 ? p.n_split : 1);
-    const int32_t* pf = prefix;
-    prefix += MOE_MAX_EXPERTS + 1;
-    if (m.n_e == 0) return;
-    v.push_back([=, &a](hipEvent_t e0, hipEvent_t e1) {
-      klaunch(tile_plan_kernel<NK>, dim3(1), dim3(256), s, e0, e1, a, m, const_cast<int32_t*>(pf));
-    });
+    if (tn == 0) return;
+    const TileMap m = tile_map(L, te0, tn, NK == 1 ? p.n_split : 1);
+    int32_t* plan = a.tile_plan + (NK == 1 ? kTilePlanInts : 0);
     v.push_back([=, &a](hipEvent_t e0, hipEvent_t e1) {
       klaunch(ffn_tile_kernel<2 * NM, NK>, dim3(static_cast<unsigned>(tile_grid())), dim3(64 * kTileWaves), s,
-              e0, e1, a, m, pf);
+              e0, e1, a, m, static_cast<const int32_t*>(plan), plan + kTilePlanInts - 1);
     });
   };
   // streaming path: one launch for every expert set that streams
@@ -420,7 +404,7 @@ int ffn_entry(const moe_layer_t* L, const uint16_t* x, int32_t T, int32_t k,
   a.xsum = reinterpret_cast<float*>(w);
   a.h = reinterpret_cast<uint16_t*>(w + p.xsum_bytes);
   a.hsum = reinterpret_cast<float*>(w + p.xsum_bytes + p.h_bytes);
-  a.tile_prefix = reinterpret_cast<int32_t*>(w + p.xsum_bytes + p.h_bytes + p.hsum_bytes);
+  a.tile_plan = reinterpret_cast<int32_t*>(w + p.xsum_bytes + p.h_bytes + p.hsum_bytes);
   a.x16 = reinterpret_cast<const uint16_t*>(w + p.xsum_bytes + p.h_bytes + p.hsum_bytes + p.tile_bytes);
   a.n_split_out = p.n_split;
   a.o = o;

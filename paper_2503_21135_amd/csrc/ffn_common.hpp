@@ -38,7 +38,7 @@ struct FfnArgs {
   float* o;
   int64_t split_stride;
   int n_split_out;     // K slices of the down projection: slices of o the combine adds
-  int32_t* tile_prefix;   // workspace: 4 x (MOE_MAX_EXPERTS + 1) item prefixes
+  int32_t* tile_plan;   // workspace: 2 x kTilePlanInts, the tile kernel's plan of each stage
   const uint16_t* x16;  // [T][d] fp16 copy of x (tile kernel; row of permuted row p: perm[p])
   int32_t* status;      // device status word or null: MOE_ERR_RANGE when an fp16 operand overflows
   uint32_t x_bytes, h_bytes, xsum_bytes, hsum_bytes, x16_bytes;   // resource sizes (< 2^31)
@@ -302,6 +302,10 @@ constexpr int kTileLdsStages = kTileWgPerCu == 1 ? 3 : 2;
 constexpr int kXcds = 8;
 constexpr int kSuper = 8;
 
+// Plan of one tile launch: item prefix [MOE_MAX_EXPERTS + 1], expert order
+// [MOE_MAX_EXPERTS], hand-out counter.
+constexpr int kTilePlanInts = 2 * (MOE_MAX_EXPERTS + 1);
+
 // Experts e0 .. e0+n_e-1 of one tile launch; bits[e - e0].
 struct TileMap {
   int e0, n_e;
@@ -321,14 +325,11 @@ __global__ void __launch_bounds__(256)
 group_sum_kernel(FfnArgs a, const uint16_t* __restrict__ in, const int32_t* __restrict__ perm,
                  int64_t ld, int p0, int p1, int K, int p_split, int K2, float* __restrict__ out);
 
-__global__ void __launch_bounds__(256) gather_f16_kernel(FfnArgs a, int T);
-
-template <int NK>
-__global__ void __launch_bounds__(256) tile_plan_kernel(FfnArgs a, TileMap map, int32_t* __restrict__ prefix);
+__global__ void __launch_bounds__(256) tile_prep_kernel(FfnArgs a, TileMap map, int T, int32_t* __restrict__ plan);
 
 template <int NM2, int NK>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
-ffn_tile_kernel(FfnArgs a, TileMap map, const int32_t* __restrict__ prefix);
+ffn_tile_kernel(FfnArgs a, TileMap map, const int32_t* __restrict__ plan, int32_t* __restrict__ counter);
 
 }  // namespace ffn
 }  // namespace moe

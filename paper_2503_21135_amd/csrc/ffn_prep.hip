@@ -1,6 +1,5 @@
-// ffn_prep.hip -- activation preparation of moe_expert_ffn_mixed: fp32 group
-// sums of the activation rows the streaming kernel reads, and the fp16 copy of
-// the token rows the tile kernel reads.
+// ffn_prep.hip -- activation preparation of the streaming kernel: fp32 group
+// sums of the activation rows it reads.
 #include "ffn_common.hpp"
 
 namespace moe {
@@ -46,32 +45,6 @@ group_sum_kernel(FfnArgs a, const uint16_t* __restrict__ in, const int32_t* __re
 #pragma unroll
   for (int off = lanes / 2; off >= 1; off >>= 1) s = s + __shfl_xor(s, off, kWave);
   if (live && q == 0) out[static_cast<int64_t>(j) * a.rows + p] = s;
-}
-
-// x16[t][c] = fp16(x[t][c]) for the T tokens, the activation operand of the
-// tile kernel, which reaches the row of permuted row p through perm[p] (one
-// copy per token instead of one per routed and shared row; exact for
-// |x| < 65504, the bf16 values being a subset of fp16's in that range); 8
-// values per thread.
-__global__ void __launch_bounds__(256) gather_f16_kernel(FfnArgs a, int T) {
-  const int per_row = a.d / 8;
-  const int64_t id = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (id >= static_cast<int64_t>(T) * per_row) return;
-  const int p = static_cast<int>(id / per_row);
-  const int c = static_cast<int>(id % per_row) * 8;
-  const u32x4 v = *reinterpret_cast<const u32x4*>(a.x + static_cast<int64_t>(p) * a.d + c);
-  u32x4 o;
-  bool bad = false;
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const float fl = bf16_lo(v[i]), fh = bf16_hi(v[i]);
-    bad = bad || !fp16_finite(fl) || !fp16_finite(fh);
-    const uint32_t lo = __builtin_bit_cast(uint16_t, static_cast<_Float16>(fl));
-    const uint32_t hi = __builtin_bit_cast(uint16_t, static_cast<_Float16>(fh));
-    o[i] = lo | (hi << 16);
-  }
-  *reinterpret_cast<u32x4*>(const_cast<uint16_t*>(a.x16) + static_cast<int64_t>(p) * a.d + c) = o;
-  if (bad && a.status) *a.status = MOE_ERR_RANGE;
 }
 
 template __global__ void group_sum_kernel<2>(FfnArgs, const uint16_t*, const int32_t*, int64_t, int, int, int,

@@ -116,34 +116,102 @@ __device__ __forceinline__ TileWaves<NK> tile_waves(const FfnArgs& a, int e, int
   return w;
 }
 
-// Items of expert e: (row blocks of eight waves) x (token tiles) x (K
-// slices); the exclusive prefix over the launch's experts goes to
-// prefix[0 .. n_e].
+// Items of expert map.e0 + i of one stage: (row blocks of eight waves) x
+// (token tiles) x (K slices).
 template <int NK>
-__global__ void __launch_bounds__(256) tile_plan_kernel(FfnArgs a, TileMap map, int32_t* __restrict__ prefix) {
-  __shared__ int cnt[MOE_MAX_EXPERTS];
-  const int i = threadIdx.x;
-  int items = 0;
+__device__ __forceinline__ int tile_items(const FfnArgs& a, int e, int tiles, int n_split) {
+  const TileWaves<NK> w = tile_waves<NK, false>(a, e, NK == 1 ? a.d : (e < a.E ? a.f : a.fs));
+  return tiles * ((w.pre[TileWaves<NK>::NC] + kTileWaves - 1) / kTileWaves) * n_split;
+}
+
+// Relative cost of an expert's items: the 32-token blocks of its largest token
+// tile, then the width (one-width layers at 4096 tokens run at 1183 / 1090 /
+// 956 / 947 / 875 TFLOP/s at 2 / 4 / 8 / 3 / 6 bits).
+__device__ __forceinline__ int tile_cost(int n_tok, int bits) {
+  const int blocks = (min(n_tok, kTileTok) + 31) / 32;
+  return 16 * blocks + (bits == 2 ? 0 : bits == 4 ? 5 : bits == 6 ? 22 : 16);
+}
+
+#if !defined(MOE_FFN_NM) || MOE_FFN_NM == 2   // one copy of the kernel that is no template
+// x16[t][c] = fp16(x[t][c]) for the T tokens, the activation operand of the
+// tile kernel, which reaches the row of permuted row p through perm[p] (one
+// copy per token instead of one per routed and shared row; exact for
+// |x| < 65504, the bf16 values being a subset of fp16's in that range); 8
+// values per thread.
+__device__ __forceinline__ void gather_f16(const FfnArgs& a, int T) {
+  const int per_row = a.d / 8;
+  const int64_t id = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (id >= static_cast<int64_t>(T) * per_row) return;
+  const int p = static_cast<int>(id / per_row);
+  const int c = static_cast<int>(id % per_row) * 8;
+  const u32x4 v = *reinterpret_cast<const u32x4*>(a.x + static_cast<int64_t>(p) * a.d + c);
+  u32x4 o;
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    const float fl = bf16_lo(v[i]), fh = bf16_hi(v[i]);
+    bad = bad || !fp16_finite(fl) || !fp16_finite(fh);
+    const uint32_t lo = __builtin_bit_cast(uint16_t, static_cast<_Float16>(fl));
+    const uint32_t hi = __builtin_bit_cast(uint16_t, static_cast<_Float16>(fh));
+    o[i] = lo | (hi << 16);
+  }
+  *reinterpret_cast<u32x4*>(const_cast<uint16_t*>(a.x16) + static_cast<int64_t>(p) * a.d + c) = o;
+  if (bad && a.status) *a.status = MOE_ERR_RANGE;
+}
+
+// Blocks [0, gridDim.x - 1): the fp16 copy of the T token rows.  Last block:
+// the work plan of both stages, plan[stage] = {prefix[0 .. n_e], order[0 ..
+// n_e)} (stage 0 gate/up, 1 down): the launch's experts by falling item cost
+// and the exclusive prefix of their items in that order, so that the items
+// handed out last, which end the launch, are the short ones; and the hand-out
+// counters of both stages, zeroed.
+__global__ void __launch_bounds__(256) tile_prep_kernel(FfnArgs a, TileMap map, int T, int32_t* __restrict__ plan) {
+  if (blockIdx.x + 1 < gridDim.x) {
+    gather_f16(a, T);
+    return;
+  }
+  __shared__ int key[MOE_MAX_EXPERTS], sorted[2][MOE_MAX_EXPERTS], wave_sum[2][4];
+  const int i = threadIdx.x, lane = i & 63, wv = i >> 6;
+  const int e = map.e0 + i;
+  if (i < 2) plan[(i + 1) * kTilePlanInts - 1] = 0;   // the stage's hand-out counter
+  int items[2] = {0, 0}, my_key = -1;
   if (i < map.n_e) {
-    const int e = map.e0 + i;
     const int n_tok = a.offsets[e + 1] - a.offsets[e];
     const int tiles = (n_tok + kTileTok - 1) / kTileTok;
-    const int R = NK == 1 ? a.d : (e < a.E ? a.f : a.fs);
-    const TileWaves<NK> w = tile_waves<NK, false>(a, e, R);
-    items = tiles * ((w.pre[TileWaves<NK>::NC] + kTileWaves - 1) / kTileWaves) * map.n_split;
+    items[0] = tile_items<2>(a, e, tiles, 1);
+    items[1] = tile_items<1>(a, e, tiles, map.n_split);
+    my_key = tile_cost(n_tok, map.bits[i]);
   }
-  if (i < MOE_MAX_EXPERTS) cnt[i] = items;
+  key[i] = my_key;
   __syncthreads();
-  if (i == 0) {
-    int acc = 0;
-    for (int j = 0; j < map.n_e; j++) {
-      const int v = cnt[j];
-      prefix[j] = acc;
-      acc += v;
+  int rank = 0;
+  for (int j = 0; j < map.n_e; j++) rank += (key[j] > my_key || (key[j] == my_key && j < i)) ? 1 : 0;
+  if (i < map.n_e) {
+    for (int st = 0; st < 2; st++) {
+      sorted[st][rank] = items[st];
+      plan[st * kTilePlanInts + MOE_MAX_EXPERTS + 1 + rank] = i;
     }
-    prefix[map.n_e] = acc;
+  }
+  __syncthreads();
+  int incl[2], own[2];
+  for (int st = 0; st < 2; st++) {
+    own[st] = incl[st] = i < map.n_e ? sorted[st][i] : 0;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+      const int o = __shfl_up(incl[st], off, kWave);
+      if (lane >= off) incl[st] += o;
+    }
+    if (lane == kWave - 1) wave_sum[st][wv] = incl[st];
+  }
+  __syncthreads();
+  for (int st = 0; st < 2; st++) {
+    int before = 0;
+    for (int w = 0; w < wv; w++) before += wave_sum[st][w];
+    if (i < map.n_e) plan[st * kTilePlanInts + i] = before + incl[st] - own[st];
+    if (i == map.n_e - 1) plan[st * kTilePlanInts + map.n_e] = before + incl[st];
   }
 }
+#endif
 
 // One lane's source of one kind: resources, {s, z} group stride and offsets.
 struct TSrc {
@@ -527,7 +595,7 @@ __device__ __forceinline__ void tile_item(const FfnArgs& a, const TileLds& lds, 
 // kind j reads the 8-bit copies; down class 1 = copies.  The item's stage
 // count: the narrow widths' three stages where every wave of the item is of
 // class 0, else two.  The token tile of the item (an expert's last tile is
-// partial) picks one, two or four 32-token blocks.
+// partial) picks one to four 32-token blocks.
 template <int NM2, int NK, int B>
 __device__ __forceinline__ void tile_dispatch(const FfnArgs& a, const TileLds& lds, int e, int cls, bool base_item,
                                               int wpos, int wend, int R, int t0, int t1, int sp, int n_split) {
@@ -536,6 +604,7 @@ __device__ __forceinline__ void tile_dispatch(const FfnArgs& a, const TileLds& l
     constexpr int NS = decltype(ns)::value, W0 = decltype(w0)::value, W1 = decltype(w1)::value;
     if (nt <= 32) tile_item<NM2, NK, NS, W0, W1, 1>(a, lds, e, c0, c1, B, wpos, wend, R, t0, t1, sp, n_split);
     else if (nt <= 64) tile_item<NM2, NK, NS, W0, W1, 2>(a, lds, e, c0, c1, B, wpos, wend, R, t0, t1, sp, n_split);
+    else if (nt <= 96) tile_item<NM2, NK, NS, W0, W1, 3>(a, lds, e, c0, c1, B, wpos, wend, R, t0, t1, sp, n_split);
     else tile_item<NM2, NK, NS, W0, W1, 4>(a, lds, e, c0, c1, B, wpos, wend, R, t0, t1, sp, n_split);
   };
   using WB = std::integral_constant<int, B>;
@@ -559,27 +628,46 @@ __device__ __forceinline__ void tile_dispatch(const FfnArgs& a, const TileLds& l
 // first one's load and LDS latencies.
 template <int NM2, int NK>
 __global__ void __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu(2)))
-ffn_tile_kernel(FfnArgs a, TileMap map, const int32_t* __restrict__ prefix) {
+ffn_tile_kernel(FfnArgs a, TileMap map, const int32_t* __restrict__ plan, int32_t* __restrict__ counter) {
   __shared__ __attribute__((aligned(16))) u32x4 st0[TileStage<NM2>::SLOTS];
   __shared__ __attribute__((aligned(16))) u32x4 st1[TileStage<NM2>::SLOTS];
   __shared__ __attribute__((aligned(16))) u32x4 st2[kTileLdsStages == 3 ? TileStage<NM2>::SLOTS : 1];
-  __shared__ int pre[MOE_MAX_EXPERTS + 1];
+  __shared__ int pre[MOE_MAX_EXPERTS + 1], ord[MOE_MAX_EXPERTS], next;
   const TileLds lds{st0, st1, st2};
-  for (int i = threadIdx.x; i <= map.n_e; i += blockDim.x) pre[i] = prefix[i];
+  for (int i = threadIdx.x; i <= map.n_e; i += blockDim.x) {
+    pre[i] = plan[i];
+    if (i < map.n_e) ord[i] = plan[MOE_MAX_EXPERTS + 1 + i];
+  }
   __syncthreads();
   const int total = pre[map.n_e];
   const int G = gridDim.x;   // a multiple of kXcds
   const int per = G / kXcds;
   const int xcd = blockIdx.x % kXcds, loc = blockIdx.x / kXcds;
+  // Full rounds go by a fixed stride (items that run together share code and
+  // activation rows), all but the last; the rest are handed out one by one to
+  // whichever workgroup is free: items of one kind differ by up to 2x in time
+  // (partial row blocks, switched rows, HBM), and workgroups with a fixed share
+  // waited for the slowest one (with 96-token tiles and costly items first,
+  // fixed -> handed out: Mixtral-shaped layer at 333 tokens, 1.8 rounds, gate/up
+  // 279 -> 271 us, down 184 -> 177; at 4096 tokens, 15 rounds, the whole call
+  // 3.00 -> 2.86 ms).
+  const int n_fixed = max(total / G - 1, 0);
   for (int it = 0;; it++) {
-    const int item = it * G + xcd * per + loc;
-    if (item >= total) break;
-    int lo = 0, hi = map.n_e - 1;   // last expert whose prefix is <= item
+    int item;
+    if (it < n_fixed) {
+      item = it * G + xcd * per + loc;
+    } else {
+      if (threadIdx.x == 0) next = n_fixed * G + atomicAdd(counter, 1);
+      tile_barrier();   // every wave has read `next` of the previous item barriers ago
+      item = uni(next);
+      if (item >= total) break;
+    }
+    int lo = 0, hi = map.n_e - 1;   // last plan entry whose prefix is <= item
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
       if (pre[mid] <= item) lo = mid; else hi = mid - 1;
     }
-    const int e = map.e0 + lo;
+    const int ei = uni(ord[lo]), e = map.e0 + ei;
     int local = item - pre[lo];
     const int seg0 = uni(a.offsets[e]), seg1 = uni(a.offsets[e + 1]);
     const int tiles = (seg1 - seg0 + kTileTok - 1) / kTileTok;
@@ -618,7 +706,7 @@ ffn_tile_kernel(FfnArgs a, TileMap map, const int32_t* __restrict__ prefix) {
     if (dead) cls = 0;
     const bool base_item = min((rb + 1) * kTileWaves, n_w) <= w.pre[1];
     const int t0 = seg0 + tt * kTileTok, t1 = min(t0 + kTileTok, seg1);
-    const int B = map.bits[e - map.e0];
+    const int B = map.bits[ei];
     if (B == 8) tile_dispatch<NM2, NK, 8>(a, lds, e, cls, base_item, wpos, wend, R, t0, t1, sp, map.n_split);
     else if (NM2 == 4 && B == 16) {   // unquantized experts need group 64
       if constexpr (NM2 == 4)
@@ -636,14 +724,12 @@ ffn_tile_kernel(FfnArgs a, TileMap map, const int32_t* __restrict__ prefix) {
 // Instantiations: every group size by default; a build may compile this file
 // once per group size (MOE_FFN_NM = 2 or 4, that is 64 or 128).
 #if !defined(MOE_FFN_NM) || MOE_FFN_NM == 2
-template __global__ void tile_plan_kernel<1>(FfnArgs, TileMap, int32_t*);
-template __global__ void tile_plan_kernel<2>(FfnArgs, TileMap, int32_t*);
-template __global__ void ffn_tile_kernel<4, 1>(FfnArgs, TileMap, const int32_t*);
-template __global__ void ffn_tile_kernel<4, 2>(FfnArgs, TileMap, const int32_t*);
+template __global__ void ffn_tile_kernel<4, 1>(FfnArgs, TileMap, const int32_t*, int32_t*);
+template __global__ void ffn_tile_kernel<4, 2>(FfnArgs, TileMap, const int32_t*, int32_t*);
 #endif
 #if !defined(MOE_FFN_NM) || MOE_FFN_NM == 4
-template __global__ void ffn_tile_kernel<8, 1>(FfnArgs, TileMap, const int32_t*);
-template __global__ void ffn_tile_kernel<8, 2>(FfnArgs, TileMap, const int32_t*);
+template __global__ void ffn_tile_kernel<8, 1>(FfnArgs, TileMap, const int32_t*, int32_t*);
+template __global__ void ffn_tile_kernel<8, 2>(FfnArgs, TileMap, const int32_t*, int32_t*);
 #endif
 
 }  // namespace ffn

@@ -278,6 +278,33 @@ def test_routed_token_tiles_split_skewed(orc):
     assert err <= TOL and err <= DIAG_STREAM
 
 
+@pytest.mark.parametrize("T", [257, 260, 333, 388, 520])
+def test_tile_token_blocks(orc, T):
+    # 65 to 130 tokens per expert on the tile kernel: last tiles of one to four
+    # 32-token blocks, and fewer items than workgroups (all handed out one by
+    # one); 8-, 6-, 4-, 3- and 2-bit experts; the hand-out starts afresh on a
+    # second call
+    import dataclasses
+    import paper_2503_21135_amd as P
+    cfg = dataclasses.replace(mi.TINY6, name="tile-blocks", cfg_id=11, n_experts=8, n_shared=0,
+                              bits_literal=(8, 4, 6, 2, 3, 4, 8, 2))
+    inp = mi.LayerInputs(cfg)
+    layer = P.MoELayer(inp)
+    layer.set_epoch(0)
+    rs = oracle_row_slots(orc, inp)
+    x = mi.make_x(cfg, T, stream=955)
+    bias = np.linspace(-0.15, 0.15, 8).astype(np.float32)   # uneven loads
+    y, b = _run(layer, x, bias)
+    res = orc.layer_forward(inp, x, bias=bias, row_slot=rs)
+    routing_matches(layer, res, b)
+    loads = np.diff(res["offsets"])[:8]
+    err = rel_l2(y, res["y"])
+    print("tile blocks, loads", loads.tolist(), "rel_l2", err, flush=True)
+    assert err <= TOL and err <= DIAG_TILE
+    again, _ = _run(layer, x, bias)
+    assert np.array_equal(y.view(np.uint32), again.view(np.uint32))
+
+
 def test_tile_sets_with_split_k(orc):
     # 4 routed experts (8/4/6/2-bit) + 1 shared, d_ff = 2048, 64 tokens: the
     # routed experts expect 32 tokens and the shared one sees 64, so both
