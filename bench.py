@@ -908,7 +908,7 @@ def main():
     sptr = stream.cuda_stream
     hip = HipEvents()
     K, W = args.steps, args.warmup
-    n_stage = 5                 # FFN stage boundaries: xsum | gate/up | hsum | down |
+    n_stage = 5                 # FFN stage boundaries: preparation | gate/up | (none) | down |
     b = layer.buffers(wk.tokens)
 
     def step(evs=None):
@@ -975,7 +975,7 @@ def main():
     tokens_per_s = wk.tokens / (ms_per_step * 1e-3)
     log("ms/step %.4f (wall %.4f, host enqueue %.4f); gate/up launch %.4f ms" %
         (ms_per_step, wall / K * 1e3, enqueue / K * 1e3, gu_ms))
-    log("diagnostic pass stages ms: xsum %.4f gate/up %.4f hsum %.4f down %.4f; step %.4f" %
+    log("diagnostic pass stages ms: preparation %.4f gate/up %.4f between %.4f down %.4f; step %.4f" %
         (*st, float(layer_ms.mean())))
     log("gate/up %.1f GB/s %.1f TFLOP/s; FFN %.1f GB/s; %.2f TFLOP/s" %
         (achieved_gbs, achieved_tf, ffn_gbs, flops / (ffn_ms * 1e-3) / 1e12))

@@ -340,7 +340,7 @@ int moe_expert_ffn_mixed(const moe_layer_t* L, const uint16_t* x, int32_t T,
  * arguments, results and errors otherwise.
  *   events    host array of n_events hipEvent_t handles (as void*), each
  *             created by the caller; NULL entries are skipped:
- *             [0] begin of the activation group-sum launch,
+ *             [0] begin of the activation preparation launch (tile path),
  *             [1] begin of the first gate/up launch,
  *             [2] end of the last gate/up launch,
  *             [3] begin of the first down launch,

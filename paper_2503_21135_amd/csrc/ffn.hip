@@ -22,7 +22,7 @@ struct Plan {
   int n_split;
   int nt_routed, nt_shared;   // token tiles of the streaming kernel, 0: tile kernel
   int tt_routed, tt_shared;   // workgroup sets per row block, each taking every n-th 32-token tile
-  size_t xsum_bytes, h_bytes, hsum_bytes, tile_bytes, x16_bytes, total;
+  size_t reserved[2], h_bytes, tile_bytes, x16_bytes, total;
 };
 
 // Shared experts with up to this many tokens stream, one workgroup set per
@@ -118,13 +118,15 @@ Plan make_plan(const moe_layer_t* L, int T, int k) {
     p.n_split = nsd;
   }
   const int64_t hcols = Tk * L->d_ff + static_cast<int64_t>(S) * T * L->d_ff_shared;
-  p.xsum_bytes = align256(sizeof(float) * static_cast<size_t>(rows) * (L->d_model / g));
+  // not used: part of the size, so that the workspace a caller has sized once,
+  // and the batches that fit the fixed no-allocation array, stay the same
+  p.reserved[0] = align256(sizeof(float) * static_cast<size_t>(rows) * (L->d_model / g));
+  p.reserved[1] = align256(sizeof(float) * static_cast<size_t>(rows) * (fmax / g));
   p.h_bytes = align256(sizeof(uint16_t) * static_cast<size_t>(hcols));
-  p.hsum_bytes = align256(sizeof(float) * static_cast<size_t>(rows) * (fmax / g));
   p.tile_bytes = align256(sizeof(int32_t) * 2 * kTilePlanInts);
   const bool tiled = p.nt_routed == 0 || (S > 0 && p.nt_shared == 0);
   p.x16_bytes = tiled ? align256(sizeof(uint16_t) * static_cast<size_t>(T) * L->d_model) : 0;
-  p.total = p.xsum_bytes + p.h_bytes + p.hsum_bytes + p.tile_bytes + p.x16_bytes + 256;
+  p.total = p.reserved[0] + p.reserved[1] + p.h_bytes + p.tile_bytes + p.x16_bytes + 256;
   return p;
 }
 
@@ -263,10 +265,9 @@ void issue(const std::vector<Launch>& v, hipEvent_t start, hipEvent_t stop, hipS
 template <int NM>
 void launch_all(const FfnArgs& a, const Plan& p, const moe_layer_t* L, int T, hipStream_t s,
                 hipEvent_t* ev, int n_ev) {
-  constexpr int g = NM * 32;
   const int S = a.S;
   auto event = [&](int i) -> hipEvent_t { return (ev && i < n_ev) ? ev[i] : nullptr; };
-  std::vector<Launch> xsum, gate_up, hsum, down;
+  std::vector<Launch> prep, gate_up, down;
   // the experts that take the tile kernel -- routed, shared, or both in one
   // launch (routed first), so that one persistent grid balances all their items
   const bool tile_r = p.nt_routed == 0, tile_s = S > 0 && p.nt_shared == 0;
@@ -274,20 +275,10 @@ void launch_all(const FfnArgs& a, const Plan& p, const moe_layer_t* L, int T, hi
   if (tn > 0) {   // the fp16 copy of the token rows and both stages' plans, one launch
     const TileMap m = tile_map(L, te0, tn, p.n_split);
     const unsigned nb = static_cast<unsigned>(cdiv(static_cast<int64_t>(T) * (a.d / 8), 256)) + 1;
-    xsum.push_back([=, &a](hipEvent_t e0, hipEvent_t e1) {
+    prep.push_back([=, &a](hipEvent_t e0, hipEvent_t e1) {
       klaunch(tile_prep_kernel, dim3(nb), dim3(256), s, e0, e1, a, m, T, a.tile_plan);
     });
   }
-  // group sums [d/g][rows] of the rows that stream
-  auto prep = [&](int p0, int p1) {
-    if (p1 <= p0) return;
-    const int64_t n = static_cast<int64_t>(p1 - p0) * (a.d / g) * (g / 8);
-    xsum.push_back([=, &a](hipEvent_t e0, hipEvent_t e1) {
-      klaunch(group_sum_kernel<NM>, dim3(static_cast<unsigned>(cdiv(n, 256))), dim3(256), s, e0, e1,
-              a, a.x, a.perm, static_cast<int64_t>(a.d), p0, p1, a.d, p1, a.d, const_cast<float*>(a.xsum));
-    });
-  };
-  if (!(tile_r && (tile_s || S == 0))) prep(tile_r ? a.Tk : 0, tile_s ? a.Tk : a.rows);
   auto add_tile = [&](std::vector<Launch>& v, auto nk) {
     constexpr int NK = decltype(nk)::value;
     if (tn == 0) return;
@@ -318,26 +309,10 @@ void launch_all(const FfnArgs& a, const Plan& p, const moe_layer_t* L, int T, hi
   using one = std::integral_constant<int, 1>;
   add_tile(gate_up, two{});
   add_stream(gate_up, two{}, 1);
-  {  // group sums of h, [max(f,fs)/g][rows], for the rows the streaming kernel reads
-    // (routed rows f wide, shared rows fs wide; one launch when both stream)
-    auto hs = [&](int p0, int p1) {
-      const int64_t n = static_cast<int64_t>(p1 - p0) * (std::max(a.f, a.fs) / g) * (g / 8);
-      hsum.push_back([=, &a](hipEvent_t e0, hipEvent_t e1) {
-        klaunch(group_sum_kernel<NM>, dim3(static_cast<unsigned>(cdiv(n, 256))), dim3(256), s, e0, e1,
-                a, static_cast<const uint16_t*>(a.h), static_cast<const int32_t*>(nullptr),
-                int64_t{0}, p0, p1, a.f, a.Tk, a.fs, a.hsum);
-      });
-    };
-    const bool rs = p.nt_routed != 0 && a.Tk > 0, ss = S > 0 && p.nt_shared != 0;
-    if (rs && ss) hs(0, a.rows);
-    else if (rs) hs(0, a.Tk);
-    else if (ss) hs(a.Tk, a.rows);
-  }
   add_tile(down, one{});
   add_stream(down, one{}, p.n_split);
-  issue(xsum, event(0), nullptr, s);
+  issue(prep, event(0), nullptr, s);
   issue(gate_up, event(1), event(2), s);
-  issue(hsum, nullptr, nullptr, s);
   issue(down, event(3), event(4), s);
 }
 
@@ -401,25 +376,21 @@ int ffn_entry(const moe_layer_t* L, const uint16_t* x, int32_t T, int32_t k,
   a.rows = T * (k + L->n_shared);
   char* w = static_cast<char*>(ws);
   w = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(w) + 255) & ~static_cast<uintptr_t>(255));
-  a.xsum = reinterpret_cast<float*>(w);
-  a.h = reinterpret_cast<uint16_t*>(w + p.xsum_bytes);
-  a.hsum = reinterpret_cast<float*>(w + p.xsum_bytes + p.h_bytes);
-  a.tile_plan = reinterpret_cast<int32_t*>(w + p.xsum_bytes + p.h_bytes + p.hsum_bytes);
-  a.x16 = reinterpret_cast<const uint16_t*>(w + p.xsum_bytes + p.h_bytes + p.hsum_bytes + p.tile_bytes);
+  a.h = reinterpret_cast<uint16_t*>(w);
+  a.tile_plan = reinterpret_cast<int32_t*>(w + p.h_bytes);
+  a.x16 = reinterpret_cast<const uint16_t*>(w + p.h_bytes + p.tile_bytes);
   a.n_split_out = p.n_split;
   a.o = o;
   a.split_stride = static_cast<int64_t>(T) * (k + L->n_shared) * L->d_model;
   {  // sizes of the buffer resources; every one must stay below 2^31 bytes
     const int64_t lim = int64_t{1} << 31;
     const int64_t xb = static_cast<int64_t>(T) * L->d_model * 2;
-    if (xb >= lim || static_cast<int64_t>(p.h_bytes) >= lim || static_cast<int64_t>(p.xsum_bytes) >= lim ||
-        static_cast<int64_t>(p.hsum_bytes) >= lim || static_cast<int64_t>(p.x16_bytes) >= lim)
+    if (xb >= lim || static_cast<int64_t>(p.h_bytes) >= lim || static_cast<int64_t>(p.x16_bytes) >= lim ||
+        static_cast<int64_t>(p.reserved[0]) >= lim || static_cast<int64_t>(p.reserved[1]) >= lim)
       return MOE_ERR_ARG;
     a.x16_bytes = static_cast<uint32_t>(p.x16_bytes);
     a.x_bytes = static_cast<uint32_t>(xb);
     a.h_bytes = static_cast<uint32_t>(p.h_bytes);
-    a.xsum_bytes = static_cast<uint32_t>(p.xsum_bytes);
-    a.hsum_bytes = static_cast<uint32_t>(p.hsum_bytes);
     for (int kd = 0; kd < 3; kd++) {
       const int64_t K = kd == MOE_KIND_DOWN ? L->d_ff : L->d_model;
       const int64_t cb = static_cast<int64_t>(L->kind[kd].n_slots) * 4 * code_row_words(K, 8);

@@ -1,7 +1,7 @@
 // ffn_common.hpp -- types, constants and device helpers shared by the
 // expert-FFN kernels (ffn_stream.hip: the streaming kernel for experts with
-// few tokens and the activation preparation kernels; ffn_tile.hip: the tile
-// kernel for experts with many tokens) and their host code (ffn.hip).
+// few tokens; ffn_tile.hip: the tile kernel for experts with many tokens)
+// and their host code (ffn.hip).
 #pragma once
 
 #include "common.hpp"
@@ -30,18 +30,16 @@ struct FfnArgs {
   const int32_t* order_dn;
   const int32_t* class_cnt;
   const uint16_t* x;
-  const float* xsum;   // [d/g][rows] group sums of the gathered x rows
   const int32_t* offsets;
   const int32_t* perm;
   uint16_t* h;
-  float* hsum;         // [max(f,fs)/g][rows] group sums of h rows
   float* o;
   int64_t split_stride;
   int n_split_out;     // K slices of the down projection: slices of o the combine adds
   int32_t* tile_plan;   // workspace: 2 x kTilePlanInts, the tile kernel's plan of each stage
   const uint16_t* x16;  // [T][d] fp16 copy of x (tile kernel; row of permuted row p: perm[p])
   int32_t* status;      // device status word or null: MOE_ERR_RANGE when an fp16 operand overflows
-  uint32_t x_bytes, h_bytes, xsum_bytes, hsum_bytes, x16_bytes;   // resource sizes (< 2^31)
+  uint32_t x_bytes, h_bytes, x16_bytes;   // resource sizes (< 2^31)
   uint32_t copy_bytes[3], copy_sz_bytes[3];
   int E, S, d, f, fs, group;
   int Tk;    // routed rows T*k
@@ -319,11 +317,6 @@ struct TileMap {
 template <int NM, int NT, int NK>
 __global__ void __launch_bounds__(64 * kWavesOf<NK>) __attribute__((amdgpu_waves_per_eu(2)))
 ffn_stream_kernel(FfnArgs a, WgMap map);
-
-template <int NM>
-__global__ void __launch_bounds__(256)
-group_sum_kernel(FfnArgs a, const uint16_t* __restrict__ in, const int32_t* __restrict__ perm,
-                 int64_t ld, int p0, int p1, int K, int p_split, int K2, float* __restrict__ out);
 
 __global__ void __launch_bounds__(256) tile_prep_kernel(FfnArgs a, TileMap map, int T, int32_t* __restrict__ plan);
 

@@ -202,6 +202,36 @@ struct XTile {
   float xs[2][CG][TOK];
 };
 
+// fp32 sum of the bf16 values of a group held by g/8 adjacent lanes, 8 each:
+// dot products with ones inside the lane, then a tree over the lanes (lane
+// pairs, quads, eights, sixteens); every lane gets the sum.  Every workgroup
+// forms the sums of the tokens it stages: ~16 VALU instructions per wave and
+// group at 32-token tiles, which costs the Mixtral-shaped layer's gate/up launch
+// 3 % at 64 tokens, but two launches (5 us each) less than sums made
+// beforehand: whole calls 118.2 -> 112.4 us (DeepSeek-shaped, 17 tokens),
+// 104.0 -> 99.0 (Mixtral-shaped, 1 token), 257.6 -> 252.0 (64 tokens).
+template <int CTRL>
+__device__ __forceinline__ float lane_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+
+template <int g>
+__device__ __forceinline__ float group_sum(const u32x4& v) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3F803F80u);
+  float s = 0.f;
+#pragma unroll
+  for (int c = 0; c < 4; c++) {
+    const uint32_t w = v[c];   // a bit cast of a vector element itself takes element 0 in this compiler
+    s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, s, false);
+  }
+  s = lane_add<0xB1>(s);    // quad_perm 1,0,3,2
+  s = lane_add<0x4E>(s);    // quad_perm 2,3,0,1
+  s = lane_add<0x141>(s);   // row_half_mirror
+  if constexpr (g == 128) s = lane_add<0x140>(s);   // row_mirror
+  return s;
+}
+
 // The rows at order positions [pos0, pos1) of expert e (lanes past pos1
 // idle), class cls (bit kk set: kind kk reads the 8-bit copies), token tile
 // passes over the expert's segment, K groups [g0, g1) of split sp.
@@ -218,7 +248,7 @@ __device__ __forceinline__ void stream_body(const FfnArgs& a, XTile<NM, NT>& tl,
   constexpr int S = kStages<RT, BG, BU>;
   constexpr int CG = XTile<NM, NT>::CG;
   static_assert((S == 2 || S == 4) && CG == 2, "the loop body below handles two two-group chunks");
-  static_assert(CG * TOK <= kThreads, "one thread per group-sum entry of a chunk");
+  static_assert(PPT <= g / 8, "one lane per piece writes a group sum");
   const int tid = threadIdx.x;
   const int wv = tid >> 6;
   const int lane = tid & 63;
@@ -283,9 +313,7 @@ __device__ __forceinline__ void stream_body(const FfnArgs& a, XTile<NM, NT>& tl,
       s.soff[rt] = copy ? s_copy : s_base;
     }
   }
-  const float* xsum = down ? a.hsum : a.xsum;
   const Rsrc xr = make_rsrc(down ? a.h : a.x, down ? a.h_bytes : a.x_bytes);
-  const Rsrc xsr = make_rsrc(xsum, down ? a.hsum_bytes : a.xsum_bytes);
 
   // token tiles pre.tt, pre.tt + n_tt, ... of the segment (all of them
   // when the launch has one workgroup set per row block)
@@ -303,26 +331,29 @@ __device__ __forceinline__ void stream_body(const FfnArgs& a, XTile<NM, NT>& tl,
 #pragma unroll
     for (int i = 0; i < PPT; i++)
       if (arow[i] != kOOB) arow[i] += 2u * acol;
-    const int xs_g = tid / TOK, xs_j = tid % TOK;   // xsum entry of threads < CG*TOK
-    const uint32_t xs_off = tid < CG * TOK && t0 + xs_j < seg1
-                                ? 4u * static_cast<uint32_t>(xs_g * a.rows + t0 + xs_j) : kOOB;
-    // chunk [gc, gc+CG): the chunk's first column / group goes into the scalar offset
-    auto stage_x = [&](u32x4 (&v)[PPT], float& xsv, int gc) {
-      const bool live_c = gc < g1;
-      const uint32_t xadv = live_c ? 2u * static_cast<uint32_t>(gc * g) : 0u;
-      const uint32_t sadv = live_c ? 4u * static_cast<uint32_t>(gc * a.rows) : 0u;
+    // chunk [gc, gc+CG): the chunk's first column goes into the scalar offset
+    auto stage_x = [&](u32x4 (&v)[PPT], int gc) {
+      const uint32_t xadv = gc < g1 ? 2u * static_cast<uint32_t>(gc * g) : 0u;
       const bool in_k = gc + acol / g < g1;   // the chunk's later groups may not exist
 #pragma unroll
       for (int i = 0; i < PPT; i++) v[i] = bload4(xr, in_k ? arow[i] : kOOB, xadv);
-      const bool ok = gc + xs_g < g1;
-      xsv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xsr, ok ? xs_off : kOOB, sadv, 0));
     };
-    auto write_x = [&](const u32x4 (&v)[PPT], float xsv, int buf) {
+    // Writes the chunk to LDS, and each token's group sums: the g/8 adjacent
+    // lanes that hold one group of a token add their pieces, and lane i of
+    // them writes the sum of piece i.
+    const int ql = tid % (g / 8);
+    float* const xs_dst = &tl.xs[0][acol / g][(tid + kThreads * min(ql, PPT - 1)) / (KC / 8)];
+    const bool xs_own = ql < PPT && (PIECES >= kThreads || tid < PIECES);
+    auto write_x = [&](const u32x4 (&v)[PPT], int buf) {
+      float sum = 0.f;
 #pragma unroll
-      for (int i = 0; i < PPT; i++)
+      for (int i = 0; i < PPT; i++) {
         if (PIECES >= kThreads || tid < PIECES)
           *reinterpret_cast<u32x4*>(&tl.x[buf][(tid + kThreads * i) / (KC / 8)][acol]) = v[i];
-      if (tid < CG * TOK) tl.xs[buf][xs_g][xs_j] = xsv;
+        const float s = group_sum<g>(v[i]);
+        sum = i == 0 || ql == i ? s : sum;
+      }
+      if (xs_own) xs_dst[buf * (CG * TOK)] = sum;
     };
 
     f32x4 acc[RT][NK][NT];
@@ -340,12 +371,11 @@ __device__ __forceinline__ void stream_body(const FfnArgs& a, XTile<NM, NT>& tl,
 #pragma unroll
     for (int s = 0; s < S; s++) load_stage<NM, RT, NK, BG, BU>(st[s], src, g0 + s, g0 + s < g1);
     u32x4 vx[CG == 2 ? 2 : 1][PPT];   // activations of the next chunk(s)
-    float vxs[CG == 2 ? 2 : 1];
     uint32_t szc[RT][2], szn[RT][2];   // {s, z} words of this and the next four groups
     load_sz4<RT, NK>(szc, src, g0, g1, kq);
-    stage_x(vx[0], vxs[0], g0);
-    write_x(vx[0], vxs[0], 0);
-    if constexpr (CG == 2) stage_x(vx[1], vxs[1], g0 + 2);
+    stage_x(vx[0], g0);
+    write_x(vx[0], 0);
+    if constexpr (CG == 2) stage_x(vx[1], g0 + 2);
     __syncthreads();
     auto group = [&](Stage<NM, RT, BG, BU>& s, int buf, int gg, int gi, int i4) {
       if (gi < g1 && wave_live) {   // wave-uniform; the loads below are unconditional
@@ -372,11 +402,11 @@ __device__ __forceinline__ void stream_body(const FfnArgs& a, XTile<NM, NT>& tl,
 #pragma unroll
       for (int c = 0; c < 2; c++) {   // chunk c of the iteration sits in LDS buffer c
         // vx[c] held chunk gc+2c (written to LDS already); reuse it for gc+2c+4
-        stage_x(vx[c], vxs[c], gc + 2 * c + 4);
+        stage_x(vx[c], gc + 2 * c + 4);
         group(st[(2 * c) % S], c, 0, gc + 2 * c, 2 * c);
         if (c == 0) load_sz4<RT, NK>(szn, src, gc + 4, g1, kq);
         group(st[(2 * c + 1) % S], c, 1, gc + 2 * c + 1, 2 * c + 1);
-        write_x(vx[c ^ 1], vxs[c ^ 1], c ^ 1);   // chunk gc+2c+2, loaded one chunk ago
+        write_x(vx[c ^ 1], c ^ 1);   // chunk gc+2c+2, loaded one chunk ago
         __syncthreads();
       }
 #pragma unroll
