@@ -154,14 +154,115 @@ __device__ __forceinline__ void select_topk(const float* src, int E, int k, int 
   }
 }
 
+constexpr int kFusedChunks = 16; // token chunks the one-workgroup permutation holds in LDS
+
+template <int CH>
+struct PermLds {
+  uint64_t mask[CH * MOE_MAX_EXPERTS];   // per chunk and expert
+  int32_t cb[CH * MOE_MAX_EXPERTS];      // chunk bases per expert
+  int32_t seg[MOE_MAX_EXPERTS + 1];      // segment offsets, then the total
+};
+
+// Histogram, scans and stable scatter of up to CH chunks in one workgroup of
+// at least CH waves and E threads.  The segment order is the same as
+// the three-kernel path's: experts ascending, then tokens ascending, shared
+// experts last.  Each chunk keeps one 64-bit lane mask per expert (bit l set
+// when token l of the chunk chose the expert), so a count is a popcount and a
+// token's rank among the chunk's rows of an expert is the popcount of the mask
+// below its lane: no thread loops over the experts.
+template <int CH>
+__device__ __forceinline__ void permute_block(PermLds<CH>& l, const int32_t* topk_ids, int T, int E, int k, int S,
+                                              int32_t* offsets, int32_t* perm_token, int32_t* inv_perm) {
+  const int lane = threadIdx.x & 63;
+  const int n_chunks = (T + kChunk - 1) / kChunk;
+  const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  // wave c holds chunk c and keeps its choices
+  const int c = threadIdx.x >> 6;
+  const int t = c * kChunk + lane;
+  const bool live = t < T;
+  // the token's choices in registers: loops over j run to the compile-time
+  // bound with j < k as a predicate, so every load is issued at once and no
+  // array is indexed at run time
+  int mine[MOE_MAX_TOPK];
+#pragma unroll
+  for (int j = 0; j < MOE_MAX_TOPK; j++)
+    mine[j] = (live && j < k) ? topk_ids[static_cast<int64_t>(t) * k + j] : -1;
+  for (int i = threadIdx.x; i < n_chunks * E; i += blockDim.x) l.mask[i] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < MOE_MAX_TOPK; j++)
+    if (mine[j] >= 0) atomicOr(&l.mask[c * E + mine[j]], 1ull << lane);
+  __syncthreads();
+  // per expert: exclusive scan of the chunk counts
+  if (threadIdx.x < E) {
+    const int e = threadIdx.x;
+    int run = 0;
+    for (int cc = 0; cc < n_chunks; cc++) {
+      l.cb[cc * E + e] = run;
+      run += __popcll(l.mask[cc * E + e]);
+    }
+    l.seg[e] = run;
+  }
+  __syncthreads();
+  // exclusive scan of the segment sizes over experts: four per lane of wave 0
+  if (c == 0) {
+    int v[4];
+    int sum = 0;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const int e = 4 * lane + i;
+      v[i] = e < E ? l.seg[e] : 0;
+      sum += v[i];
+    }
+    int incl = sum;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+      const int o = __shfl_up(incl, off, kWave);
+      if (lane >= off) incl += o;
+    }
+    int run = incl - sum;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const int e = 4 * lane + i;
+      if (e < E) l.seg[e] = run;
+      run += v[i];
+    }
+    if (lane == kWave - 1) l.seg[MOE_MAX_EXPERTS] = incl;
+  }
+  __syncthreads();
+  const int routed = l.seg[MOE_MAX_EXPERTS];
+  for (int e = threadIdx.x; e < E; e += blockDim.x) offsets[e] = l.seg[e];
+  for (int s2 = threadIdx.x; s2 <= S; s2 += blockDim.x) offsets[E + s2] = routed + s2 * T;
+  if (!live) return;
+  const int64_t row = static_cast<int64_t>(t) * (k + S);
+#pragma unroll
+  for (int j = 0; j < MOE_MAX_TOPK; j++) {
+    if (j < k) {
+      const int i = c * E + mine[j];
+      const int p = l.seg[mine[j]] + l.cb[i] + __popcll(l.mask[i] & below);
+      perm_token[p] = t;
+      inv_perm[row + j] = p;
+    }
+  }
+  for (int s2 = 0; s2 < S; s2++) {
+    const int p = routed + s2 * T + t;
+    perm_token[p] = t;
+    inv_perm[row + k + s2] = p;
+  }
+}
+
 // One workgroup (8 waves) per token.  Wave w owns experts w, w + 8, ... and
 // computes their logits four, two or one at a time; wave 0 then selects the
-// top k and forms the weights.
+// top k and forms the weights.  A single token's workgroup also writes its
+// permutation: the launch that would otherwise do it costs
+// more than the whole permutation (routing at 1 token: 6.3 + 4.1 us in two
+// launches, 8.2 in one; 8 experts, d_model 4096).
 __global__ void __launch_bounds__(kRouteWaves * kWave)
 route_topk_kernel(const uint16_t* __restrict__ x, int T, int d, const float* __restrict__ wr,
-                  const float* __restrict__ bias, int E, int k,
-                  int32_t* __restrict__ topk_ids, float* __restrict__ topk_w) {
+                  const float* __restrict__ bias, int E, int k, int S, int32_t* topk_ids,
+                  float* __restrict__ topk_w, int32_t* offsets, int32_t* perm_token, int32_t* inv_perm) {
   __shared__ float lgs[MOE_MAX_EXPERTS];
+  __shared__ PermLds<1> l;
   const int t = blockIdx.x;
   const int lane = threadIdx.x & 63;
   const int wv = threadIdx.x >> 6;
@@ -192,8 +293,10 @@ route_topk_kernel(const uint16_t* __restrict__ x, int T, int d, const float* __r
     finish(wv + m * kRouteWaves, acc[0]);
   }
   __syncthreads();
-  if (wv != 0) return;
-  select_topk(lgs, E, k, t, lane, topk_ids, topk_w);
+  if (wv == 0) select_topk(lgs, E, k, t, lane, topk_ids, topk_w);
+  if (T > 1) return;
+  __syncthreads();   // the token's choices are written
+  permute_block(l, topk_ids, T, E, k, S, offsets, perm_token, inv_perm);
 }
 
 constexpr int kLogitWaves = 4;      // waves of a logits workgroup
@@ -537,99 +640,16 @@ route_scatter_kernel(const int32_t* __restrict__ topk_ids, int T, int E, int k, 
   }
 }
 
-constexpr int kPermWaves = 16;   // waves of the fused permutation workgroup
-constexpr int kFusedChunks = 16; // token chunks the fused path holds in LDS
+constexpr int kPermWaves = 16;   // waves of the one-workgroup permutation
 
-// Histogram, scans and stable scatter of up to kFusedChunks chunks in one
-// workgroup (batches of up to 1024 tokens).  The segment order is the same as
-// the three-kernel path's: experts ascending, then tokens ascending, shared
-// experts last.  Each chunk keeps one 64-bit lane mask per expert (bit l set
-// when token l of the chunk chose the expert), so a count is a popcount and a
-// token's rank among the chunk's rows of an expert is the popcount of the mask
-// below its lane: no thread loops over the experts.
+// The permutation of up to kFusedChunks chunks (batches of up to 1024 tokens)
+// as a launch of its own.
 __global__ void __launch_bounds__(kPermWaves * kWave)
 route_permute_fused_kernel(const int32_t* __restrict__ topk_ids, int T, int E, int k, int S,
                            int32_t* __restrict__ offsets, int32_t* __restrict__ perm_token,
                            int32_t* __restrict__ inv_perm) {
-  __shared__ uint64_t mask[kFusedChunks * MOE_MAX_EXPERTS];  // per chunk and expert
-  __shared__ int32_t cb[kFusedChunks * MOE_MAX_EXPERTS];     // chunk bases per expert
-  __shared__ int32_t seg[MOE_MAX_EXPERTS + 1];               // segment offsets, then the total
-  const int lane = threadIdx.x & 63;
-  const int n_chunks = (T + kChunk - 1) / kChunk;
-  const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  // wave c holds chunk c (n_chunks <= kPermWaves) and keeps its choices
-  const int c = threadIdx.x >> 6;
-  const int t = c * kChunk + lane;
-  const bool live = t < T;
-  // the token's choices in registers: loops over j run to the compile-time
-  // bound with j < k as a predicate, so every load is issued at once and no
-  // array is indexed at run time
-  int mine[MOE_MAX_TOPK];
-#pragma unroll
-  for (int j = 0; j < MOE_MAX_TOPK; j++)
-    mine[j] = (live && j < k) ? topk_ids[static_cast<int64_t>(t) * k + j] : -1;
-  for (int i = threadIdx.x; i < n_chunks * E; i += blockDim.x) mask[i] = 0;
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < MOE_MAX_TOPK; j++)
-    if (mine[j] >= 0) atomicOr(&mask[c * E + mine[j]], 1ull << lane);
-  __syncthreads();
-  // per expert: exclusive scan of the chunk counts
-  if (threadIdx.x < E) {
-    const int e = threadIdx.x;
-    int run = 0;
-    for (int cc = 0; cc < n_chunks; cc++) {
-      cb[cc * E + e] = run;
-      run += __popcll(mask[cc * E + e]);
-    }
-    seg[e] = run;
-  }
-  __syncthreads();
-  // exclusive scan of the segment sizes over experts: four per lane of wave 0
-  if (c == 0) {
-    int v[4];
-    int sum = 0;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int e = 4 * lane + i;
-      v[i] = e < E ? seg[e] : 0;
-      sum += v[i];
-    }
-    int incl = sum;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-      const int o = __shfl_up(incl, off, kWave);
-      if (lane >= off) incl += o;
-    }
-    int run = incl - sum;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int e = 4 * lane + i;
-      if (e < E) seg[e] = run;
-      run += v[i];
-    }
-    if (lane == kWave - 1) seg[MOE_MAX_EXPERTS] = incl;
-  }
-  __syncthreads();
-  const int routed = seg[MOE_MAX_EXPERTS];
-  for (int e = threadIdx.x; e < E; e += blockDim.x) offsets[e] = seg[e];
-  for (int s2 = threadIdx.x; s2 <= S; s2 += blockDim.x) offsets[E + s2] = routed + s2 * T;
-  if (!live) return;
-  const int64_t row = static_cast<int64_t>(t) * (k + S);
-#pragma unroll
-  for (int j = 0; j < MOE_MAX_TOPK; j++) {
-    if (j < k) {
-      const int i = c * E + mine[j];
-      const int p = seg[mine[j]] + cb[i] + __popcll(mask[i] & below);
-      perm_token[p] = t;
-      inv_perm[row + j] = p;
-    }
-  }
-  for (int s2 = 0; s2 < S; s2++) {
-    const int p = routed + s2 * T + t;
-    perm_token[p] = t;
-    inv_perm[row + k + s2] = p;
-  }
+  __shared__ PermLds<kFusedChunks> l;
+  permute_block(l, topk_ids, T, E, k, S, offsets, perm_token, inv_perm);
 }
 
 // x_perm[p] = x[perm_token[p]] (16-byte copies; d % 8 == 0).
@@ -684,6 +704,7 @@ extern "C" int moe_route_permute(const uint16_t* x, int32_t T, int32_t d, const 
   float* logits = reinterpret_cast<float*>(static_cast<char*>(ws) + 2 * half);
   const dim3 blk(4 * kWave);
   auto n_wg = [&](int tt, int te) { return static_cast<unsigned>(cdiv(T, tt) * cdiv(E, te)); };
+  bool permuted = false;
   if (T > 0 && staged && (T >= kSplitRouterMinT || E >= kSplitRouterMinE)) {
     // logits over (token block, expert block) workgroups staged through LDS,
     // then the top k per token; on small batches of few experts the second
@@ -707,9 +728,12 @@ extern "C" int moe_route_permute(const uint16_t* x, int32_t T, int32_t d, const 
                        topk_ids, topk_w);
   } else if (T > 0) {
     hipLaunchKernelGGL(route_topk_kernel, dim3(static_cast<unsigned>(T)), dim3(kRouteWaves * kWave),
-                       0, s, x, T, d, w_router, bias, E, k, topk_ids, topk_w);
+                       0, s, x, T, d, w_router, bias, E, k, S, topk_ids, topk_w, offsets, perm_token, inv_perm);
+    permuted = T == 1;
   }
-  if (n_chunks <= kFusedChunks) {
+  if (permuted) {
+    // written by the launch above
+  } else if (n_chunks <= kFusedChunks) {
     hipLaunchKernelGGL(route_permute_fused_kernel, dim3(1), dim3(kPermWaves * kWave), 0, s,
                        topk_ids, T, E, k, S, offsets, perm_token, inv_perm);
   } else {
