@@ -21,6 +21,7 @@ size_t align256(size_t v) { return (v + 255) & ~static_cast<size_t>(255); }
 struct Plan {
   int n_split;
   int nt_routed, nt_shared;   // token tiles of the streaming kernel, 0: tile kernel
+  bool vec;                   // the streaming kernel's form for batches of one or two tokens
   int tt_routed, tt_shared;   // workgroup sets per row block, each taking every n-th 32-token tile
   size_t reserved[2], h_bytes, tile_bytes, x16_bytes, total;
 };
@@ -100,6 +101,7 @@ Plan make_plan(const moe_layer_t* L, int T, int k) {
     p.nt_shared = 2;
     p.tt_shared = static_cast<int>(cdiv(T, 32));
   }
+  p.vec = T <= kVecTok;   // vec_body, whose comment has both sides measured
   // split-K slices of the down projection: where the routed experts stream
   // (few tokens, too few output rows to fill the machine), and where the
   // tile kernel's down items (token tiles x row blocks) are too few for its
@@ -175,14 +177,15 @@ int validate_layer(const moe_layer_t* L) {
 // the routed experts widest first.
 WgMap stream_map(const moe_layer_t* L, const Plan& p, bool routed, bool shared, bool down, int n_split) {
   WgMap m{};
-  const int rows1 = (down ? kWavesOf<1> : kWavesOf<2>) * 16;
+  const int rows1 = 16 * (down ? (p.vec ? kWavesOf<1, true> : kWavesOf<1, false>)
+                             : (p.vec ? kWavesOf<2, true> : kWavesOf<2, false>));
   const int E = L->n_experts, S = L->n_shared;
   m.n_split = n_split;
   m.tt_r = std::max(p.tt_routed, 1);
   m.tt_s = std::max(p.tt_shared, 1);
   m.m_r = m.tt_r * n_split;
   m.m_s = m.tt_s * n_split;
-  for (int e = 0; e < E + S; e++) m.bits[e] = static_cast<int8_t>(L->bits_host[e]);
+  for (int e = 0; e < E + S; e++) m.bits[e / 4] |= static_cast<uint32_t>(L->bits_host[e]) << (8 * (e % 4));
   if (routed) {
     const int R = down ? L->d_model : L->d_ff;
     std::vector<int> nc[2];
@@ -206,28 +209,24 @@ WgMap stream_map(const moe_layer_t* L, const Plan& p, bool routed, bool shared, 
     m.n_sw = n_sw;
   }
   int n = 0;
-  int32_t start = 0;
-  auto entry = [&](int e) {
-    const int R = down ? L->d_model : (e < E ? L->d_ff : L->d_ff_shared);
-    const int64_t nblk = cdiv(R, rows1 * stream_rt(L->bits_host[e]));
-    m.ent_e[n] = static_cast<int16_t>(e);
-    m.ent_start[n] = start;
-    start += static_cast<int32_t>(nblk * (e < E ? m.m_r : m.m_s));
-    n++;
-  };
-  if (shared)
+  auto entry = [&](int e) { m.ent[n++] = e | L->bits_host[e] << 16; };
+  if (shared) {
+    m.n_s = S;
+    m.blk_s = static_cast<int>(cdiv(down ? L->d_model : L->d_ff_shared, rows1));
     for (int s = 0; s < S; s++) entry(E + s);
-  if (routed)
+  }
+  if (routed) {
+    m.blk_r = static_cast<int>(cdiv(down ? L->d_model : L->d_ff, rows1));
     for (int b : {16, 8, 6, 4, 3, 2})
       for (int e = 0; e < E; e++)
         if (L->bits_host[e] == b) entry(e);
-  m.ent_start[n] = start;
-  m.n_ent = n;
+  }
   return m;
 }
 
-int64_t stream_grid(const WgMap& m) {
-  return static_cast<int64_t>(m.n_r) * m.n_sw * m.m_r + (m.n_ent > 0 ? m.ent_start[m.n_ent] : 0);
+int64_t stream_grid(const WgMap& m, int E) {
+  return static_cast<int64_t>(m.n_r) * m.n_sw * m.m_r + static_cast<int64_t>(m.n_s) * m.blk_s * m.m_s +
+         static_cast<int64_t>(E) * m.blk_r * m.m_r;
 }
 
 TileMap tile_map(const moe_layer_t* L, int e0, int n_e, int n_split) {
@@ -295,14 +294,15 @@ void launch_all(const FfnArgs& a, const Plan& p, const moe_layer_t* L, int T, hi
     const bool r = p.nt_routed != 0, sh = S > 0 && p.nt_shared != 0;
     if (!r && !sh) return;
     const WgMap m = stream_map(L, p, r, sh, NK == 1, nsplit);
-    const int64_t n_wg = stream_grid(m);
+    const int64_t n_wg = stream_grid(m, a.E);
     if (n_wg == 0) return;
     const int nt = std::max(r ? p.nt_routed : 0, sh ? p.nt_shared : 0);
     const dim3 grid(static_cast<unsigned>(n_wg));
     v.push_back([=, &a](hipEvent_t e0, hipEvent_t e1) {
-      const dim3 block(64 * kWavesOf<NK>);
-      if (nt == 1) klaunch(ffn_stream_kernel<NM, 1, NK>, grid, block, s, e0, e1, a, m);
-      else klaunch(ffn_stream_kernel<NM, 2, NK>, grid, block, s, e0, e1, a, m);
+      const dim3 block(64 * (p.vec ? kWavesOf<NK, true> : kWavesOf<NK, false>));
+      if (p.vec) klaunch(ffn_stream_kernel<NM, 1, NK, true>, grid, block, s, e0, e1, a, m);
+      else if (nt == 1) klaunch(ffn_stream_kernel<NM, 1, NK, false>, grid, block, s, e0, e1, a, m);
+      else klaunch(ffn_stream_kernel<NM, 2, NK, false>, grid, block, s, e0, e1, a, m);
     });
   };
   using two = std::integral_constant<int, 2>;

@@ -256,31 +256,29 @@ __device__ __forceinline__ void lds_dma16(Rsrc r, void* lds, uint32_t off, uint3
 // Waves per workgroup: four for gate/up; eight for down, whose tile of
 // activations (h) is then shared by twice the rows (measured: the down
 // launch 7 % faster, gate/up not).
-template <int NK>
-constexpr int kWavesOf = NK == 1 ? 8 : 4;
+// VEC: the kernel for batches of up to kVecTok tokens, whose waves do not share
+// activations: four.
+constexpr int kVecTok = 2;
 
-// Row tiles of 16 rows per wave for a class whose rows all read base codes
-// of width b, shared by the kernel and the host's work map.  Measured on
-// MI355X: two row tiles per wave at 3 and 4 bits and three at 2 bits
-// (workgroups streaming about as many bytes as an 8-bit one) left a layer of
-// one width unchanged and the mixed layers slower (fewer, equal workgroups
-// leave a partial last round), so every width takes one.
-__host__ __device__ constexpr int stream_rt(int b) { return b > 0 ? 1 : 1; }
+template <int NK, bool VEC>
+constexpr int kWavesOf = NK == 1 && !VEC ? 8 : 4;
 
 // Work map of one streaming launch.  Workgroups [0, n_r*n_sw*m_r) take the
 // switched classes of routed experts 0..n_r-1 (n_sw row blocks of one row
 // tile per wave per expert, m_r variants each); the rest are the class-0
-// row blocks of the entries ent_e[0..n_ent), entry i owning workgroups
-// [ent_start[i], ent_start[i+1]) after the switched section: its row blocks
-// (kWavesOf<NK> * 16 * stream_rt(bits) rows each) times its variants (m_r
-// for routed, m_s for shared experts).  A variant is a token-tile set
-// (tt_r / tt_s sets, each taking every n-th 32-token tile of the expert)
-// and a K slice (n_split).
+// row blocks of the entries: n_s shared experts with blk_s row blocks of
+// WV * 16 rows and m_s variants each, then the routed experts with blk_r
+// and m_r.  Equal blocks per entry make a workgroup's entry one division.
+// (Two or three row tiles per wave for narrow codes, so that every workgroup
+// streams about the same bytes, measured no faster: fewer, equal workgroups
+// leave a partial last round.)  A variant is a token-tile set (tt_r / tt_s
+// sets, each taking every n-th 32-token tile of the expert) and a K slice
+// (n_split).  Words of 32 bits throughout: a narrower element at a run-time
+// index is no scalar load.
 struct WgMap {
-  int n_r, n_sw, m_r, m_s, tt_r, tt_s, n_split, n_ent;
-  int32_t ent_start[MOE_MAX_EXPERTS + 1];
-  int16_t ent_e[MOE_MAX_EXPERTS];
-  int8_t bits[MOE_MAX_EXPERTS];   // bit-width of expert e (routed and shared)
+  int n_r, n_sw, m_r, m_s, tt_r, tt_s, n_split, n_s, blk_s, blk_r;
+  int32_t ent[MOE_MAX_EXPERTS];            // entry i: expert, bit-width << 16
+  uint32_t bits[MOE_MAX_EXPERTS / 4];      // bit-width of expert e: byte e % 4 of word e / 4
 };
 
 constexpr int kTileTok = 128;   // tokens per workgroup tile (four 32-token blocks)
@@ -314,8 +312,8 @@ struct TileMap {
 // ------------------------------------------------------------------ kernels
 // Defined in ffn_stream.hip and ffn_tile.hip; launched by the host code of
 // ffn.hip.
-template <int NM, int NT, int NK>
-__global__ void __launch_bounds__(64 * kWavesOf<NK>) __attribute__((amdgpu_waves_per_eu(2)))
+template <int NM, int NT, int NK, bool VEC>
+__global__ void __launch_bounds__((64 * kWavesOf<NK, VEC>)) __attribute__((amdgpu_waves_per_eu(2)))
 ffn_stream_kernel(FfnArgs a, WgMap map);
 
 __global__ void __launch_bounds__(256) tile_prep_kernel(FfnArgs a, TileMap map, int T, int32_t* __restrict__ plan);

@@ -65,6 +65,7 @@ constexpr int kStages = (RT >= 2 || BG >= 8 || BU >= 8 || BG == 6 || BU == 6) ? 
 struct Pre {
   int64_t code_off[2], sz_off[2];   // per kind of the launch
   int tt, n_tt;                     // token tile of the workgroup, when the tiles are split over workgroups
+  int row;                          // class 0: row at lane % 16 of the wave's positions
 };
 
 template <int NM, int B>
@@ -215,16 +216,23 @@ __device__ __forceinline__ float lane_add(float v) {
   return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
 }
 
-template <int g>
-__device__ __forceinline__ float group_sum(const u32x4& v) {
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3F803F80u);
-  float s = 0.f;
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// acc + sum over the 8 bf16 pairs of a and b
+__device__ __forceinline__ float dot8(const u32x4& a, const u32x4& b, float acc) {
 #pragma unroll
   for (int c = 0; c < 4; c++) {
-    const uint32_t w = v[c];   // a bit cast of a vector element itself takes element 0 in this compiler
-    s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, s, false);
+    const uint32_t x = a[c], w = b[c];   // a bit cast of a vector element itself takes element 0 in this compiler
+    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, x), __builtin_bit_cast(bf16x2, w), acc, false);
   }
+  return acc;
+}
+
+constexpr uint32_t kOnes = 0x3F803F80u;   // two bf16 1.0
+
+template <int g>
+__device__ __forceinline__ float group_sum(const u32x4& v) {
+  float s = dot8(v, u32x4{kOnes, kOnes, kOnes, kOnes}, 0.f);
   s = lane_add<0xB1>(s);    // quad_perm 1,0,3,2
   s = lane_add<0x4E>(s);    // quad_perm 2,3,0,1
   s = lane_add<0x141>(s);   // row_half_mirror
@@ -235,10 +243,10 @@ __device__ __forceinline__ float group_sum(const u32x4& v) {
 // The rows at order positions [pos0, pos1) of expert e (lanes past pos1
 // idle), class cls (bit kk set: kind kk reads the 8-bit copies), token tile
 // passes over the expert's segment, K groups [g0, g1) of split sp.
-template <int NM, int NT, int RT, int NK, int BG, int BU>
+template <int NM, int NT, int RT, int NK, int BG, int BU, int WV>
 __device__ __forceinline__ void stream_body(const FfnArgs& a, XTile<NM, NT>& tl, const Pre& pre, int e,
                                             int cls, int pos0, int pos1, int R, int sp, int n_split) {
-  constexpr int kThreads = 64 * kWavesOf<NK>;
+  constexpr int kThreads = 64 * WV;
   constexpr int g = NM * 32;
   constexpr int KC = XTile<NM, NT>::KC;
   constexpr int TOK = XTile<NM, NT>::TOK;
@@ -274,8 +282,9 @@ __device__ __forceinline__ void stream_body(const FfnArgs& a, XTile<NM, NT>& tl,
     live[rt] = pos < pos1;
     // positions past the class (pos >= pos1) are not read: for the last
     // expert's last class they would lie past the end of the order table
-    const int prow = (live[rt] && routed) ? order[static_cast<int64_t>(e) * R + pos] : 0;
-    row_id[rt] = live[rt] ? (routed ? prow : pos) : 0;
+    int prow = pre.row;
+    if (cls != 0) prow = live[rt] ? order[static_cast<int64_t>(e) * R + pos] : 0;
+    row_id[rt] = live[rt] ? prow : 0;
   }
   // a wave whose rows all lie past the class (the last workgroup of an
   // expert whose rows do not fill it) still stages activations and meets the
@@ -445,21 +454,186 @@ __device__ __forceinline__ void stream_body(const FfnArgs& a, XTile<NM, NT>& tl,
 }
 
 
-// Class 0 (both kinds on the expert's base codes) takes stream_rt(B) row
-// tiles per wave; the switched classes (one or both kinds on the 8-bit
-// copies) one.
-template <int NM, int NT, int NK, int B>
+// ------------------------------------------------------------------ one or two tokens
+// For batches of one or two tokens (kVecTok) the matrix tile would be mostly
+// padding, and the streaming body is bound by latency and by the L1: its lanes
+// hold 16 rows, so a load instruction touches 16 rows' cache lines 16 bytes at
+// a time, and the activation chunks tie four waves to a barrier.  Here a wave
+// takes its 16 rows one after another, its lanes side by side along K: four
+// lanes per group, 16 groups of a row per load (1 KB in a row at 4 bits), the
+// activations of the lane's columns in registers, no LDS and no barrier.  The
+// codes become the same exact bf16 integers, which v_dot2_f32_bf16 contracts
+// in fp32 with the lane's activations; the lane applies its group's scale and
+// zero point to its own partial sum, and the lanes' sums are added at the end.
+// Eight rows' codes are in flight.
+// Measured, whole calls, against 16-token tiles: Mixtral-shaped 94.8 -> 76.6 us
+// at 1 token and 108.4 -> 105.7 at 2, DeepSeek-shaped 57.2 -> 47.3 and 61.4 ->
+// 56.7, Qwen-shaped 62.7 -> 51.8 and 70.4 -> 59.7.  With more tokens the launch
+// has waves enough and the matrix tile's fewer instructions per weight win:
+// chosen per expert by its token count it lost 2 to 13 % from 3 to 20 tokens on
+// the DeepSeek-shaped layer and up to 6 % from 6 on the Mixtral-shaped one.
+
+// Sums of N values (a power of two, at most 64) over the wave: at each offset a
+// lane keeps half of its values and hands the other half over; value v ends in
+// the lanes l with l / (64 / N) == v.
+template <int N, int OFF, int NV>
+__device__ __forceinline__ void wave_scatter_sum(float (&v)[NV], int lane) {
+  if constexpr (OFF >= 1) {
+    constexpr int H = N > 1 ? N / 2 : 1;
+    if constexpr (N > 1) {
+      const bool hi = (lane & OFF) != 0;
+#pragma unroll
+      for (int i = 0; i < H; i++) {
+        const float send = hi ? v[i] : v[i + H];
+        const float keep = hi ? v[i + H] : v[i];
+        v[i] = keep + __shfl_xor(send, OFF, kWave);
+      }
+    } else {
+      v[0] = v[0] + __shfl_xor(v[0], OFF, kWave);
+    }
+    wave_scatter_sum<H, OFF / 2, NV>(v, lane);
+  }
+}
+
+// The rows at order positions [pos0, pos1) of expert e on its base codes,
+// TT >= the expert's n_tok tokens, K groups [g0, g1) of split sp.
+template <int NM, int NK, int B, int TT>
+__device__ __forceinline__ void vec_body(const FfnArgs& a, const Pre& pre, int e, int pos0, int pos1, int R, int sp,
+                                         int n_split, int seg0, int n_tok) {
+  constexpr int g = NM * 32;
+  constexpr int NW = kWords<NM, B>;
+  constexpr int RB = NK * TT == 4 ? 8 : 16;   // rows whose sums a lane holds at once
+  constexpr int D = 8 / NK;                   // rows in flight
+  constexpr int N = RB * TT;
+  constexpr uint32_t gcb = NM * 32 * B / 8;   // code bytes per row and group
+  const int lane = threadIdx.x & 63;
+  const int p0 = pos0 + 16 * uni(static_cast<int>(threadIdx.x >> 6));
+  if (p0 >= pos1) return;
+  const int n_rows = min(16, pos1 - p0);
+  const bool routed = e < a.E;
+  const bool down = NK == 1;
+  const int K = down ? (routed ? a.f : a.fs) : a.d;
+  const int G = K / g;
+  const int g0 = sp * G / n_split;
+  const int g1 = (sp + 1) * G / n_split;
+  const int kind0 = down ? 2 : 0;
+  // lane r holds row r (past the class: its last row, computed and not stored)
+  const int row = __shfl(pre.row, min(lane & 15, n_rows - 1));
+  const uint32_t row_bytes = 4u * static_cast<uint32_t>(code_row_words(K, B));
+  Rsrc code[NK], sz[NK];
+#pragma unroll
+  for (int kk = 0; kk < NK; kk++) {
+    const KindDev& kd = a.kd[kind0 + kk];
+    code[kk] = make_rsrc(kd.codes + uni(pre.code_off[kk]), static_cast<uint32_t>(R) * row_bytes);
+    sz[kk] = make_rsrc(kd.sz + uni(pre.sz_off[kk]), static_cast<uint32_t>(R) * G * 4u);
+  }
+  const Rsrc xr = make_rsrc(down ? a.h : a.x, down ? a.h_bytes : a.x_bytes);
+  uint32_t xrow[TT];   // byte offset of the token's row
+#pragma unroll
+  for (int t = 0; t < TT; t++) {
+    const int p = seg0 + min(t, n_tok - 1);
+    xrow[t] = uni(static_cast<uint32_t>(2 * (down ? h_row(a, p) : static_cast<int64_t>(a.perm[p]) * K)));
+  }
+  uint32_t vm = kMagic, vh = kHighMagic<B, B>;
+  asm volatile("" : "+v"(vm), "+v"(vh));
+
+  for (int rb = 0; rb < n_rows; rb += RB) {
+    float acc[NK][N];
+#pragma unroll
+    for (int kk = 0; kk < NK; kk++)
+#pragma unroll
+      for (int i = 0; i < N; i++) acc[kk][i] = 0.f;
+    for (int gc = g0; gc < g1; gc += 16) {
+      const int gi = gc + (lane >> 2);
+      const bool ok = gi < g1;   // lanes past the slice read zeros everywhere
+      const uint32_t xo = ok ? static_cast<uint32_t>(2 * (gi * g + (lane & 3) * (g / 4))) : kOOB;
+      const uint32_t co = ok ? static_cast<uint32_t>(gi) * gcb + (lane & 3) * (gcb / 4) : kOOB;
+      const uint32_t so = ok ? static_cast<uint32_t>(gi) * static_cast<uint32_t>(R) * 4u : kOOB;
+      uint32_t cw[D][NK][NW], sw[D][NK];
+      auto load = [&](int r) {
+        const uint32_t rid = static_cast<uint32_t>(__builtin_amdgcn_readlane(row, rb + r));
+#pragma unroll
+        for (int kk = 0; kk < NK; kk++) {
+          bload<NW>(cw[r % D][kk], code[kk], co, rid * row_bytes);
+          sw[r % D][kk] = __builtin_amdgcn_raw_buffer_load_b32(sz[kk], so, rid * 4u, 0);
+        }
+      };
+      u32x4 x[TT][NM];
+      float X[TT];
+#pragma unroll
+      for (int t = 0; t < TT; t++)
+#pragma unroll
+        for (int m = 0; m < NM; m++) x[t][m] = bload4(xr, ok ? xo + 16u * m : kOOB, xrow[t]);
+#pragma unroll
+      for (int r = 0; r < D; r++) load(r);
+#pragma unroll
+      for (int t = 0; t < TT; t++) {
+        X[t] = 0.f;
+#pragma unroll
+        for (int m = 0; m < NM; m++) X[t] = dot8(x[t][m], u32x4{kOnes, kOnes, kOnes, kOnes}, X[t]);
+      }
+#pragma unroll
+      for (int r = 0; r < RB; r++) {
+#pragma unroll
+        for (int kk = 0; kk < NK; kk++) {
+          u32x4 wf[kPlanes<B>][NM];
+          dequant_b<B, NM, NW>(cw[r % D][kk], wf, vm, vh);
+          const uint32_t w = sw[r % D][kk];
+          const float sc = fp16_bits_to_f32(w & 0xFFFFu);
+          const float zz = fp16_bits_to_f32(w >> 16) + kOffset<B>;
+#pragma unroll
+          for (int t = 0; t < TT; t++) {
+            float s = 0.f;   // a chain of dependent dot products per operand, then their sum
+#pragma unroll
+            for (int m = 0; m < NM; m++) {
+              float sm = 0.f;
+#pragma unroll
+              for (int pl = 0; pl < kPlanes<B>; pl++) sm = dot8(x[t][m], wf[pl][m], sm);
+              s = m == 0 ? sm : s + sm;
+            }
+            acc[kk][r * TT + t] = __fmaf_rn(sc, __fmaf_rn(-zz, X[t], s), acc[kk][r * TT + t]);
+          }
+        }
+        if (r + D < RB) load(r + D);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int kk = 0; kk < NK; kk++) wave_scatter_sum<N, kWave / 2, N>(acc[kk], lane);
+    const int v = lane / (kWave / N);
+    const int r = rb + v / TT, t = v % TT;
+    const int rid = __shfl(row, r & 15);
+    if (lane % (kWave / N) == 0 && r < n_rows && t < n_tok) {
+      const int p = seg0 + t;
+      if constexpr (down)
+        a.o[static_cast<int64_t>(sp) * a.split_stride + static_cast<int64_t>(p) * R + rid] = acc[0][0];
+      else
+        a.h[h_row(a, p) + rid] = static_cast<uint16_t>(bf16_rne(silu_mul(acc[0][0], acc[NK - 1][0])));
+    }
+  }
+}
+
+template <int NM, int NK, int B>
+__device__ __forceinline__ void vec_dispatch(const FfnArgs& a, const Pre& pre, int e, int pos0, int pos1, int R,
+                                             int sp, int n_split, int seg0, int n_tok) {
+  if (n_tok == 1) vec_body<NM, NK, B, 1>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, n_tok);
+  else vec_body<NM, NK, B, 2>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, n_tok);
+}
+
+
+// Class 0: both kinds on the expert's base codes (in the VEC kernel vec_body's);
+// the switched classes have one or both kinds on the 8-bit copies.
+template <int NM, int NT, int NK, int B, int WV, bool VEC>
 __device__ __forceinline__ void dispatch_class(const FfnArgs& a, XTile<NM, NT>& tl, const Pre& pre, int e,
                                                int cls, int pos0, int pos1, int R, int sp, int n_split) {
-  constexpr int RT0 = stream_rt(B);
   if constexpr (NK == 1) {
-    if (cls == 0) stream_body<NM, NT, RT0, 1, B, B>(a, tl, pre, e, 0, pos0, pos1, R, sp, n_split);
-    else stream_body<NM, NT, 1, 1, 8, 8>(a, tl, pre, e, 1, pos0, pos1, R, sp, n_split);
+    if (!VEC && cls == 0) stream_body<NM, NT, 1, 1, B, B, WV>(a, tl, pre, e, 0, pos0, pos1, R, sp, n_split);
+    else stream_body<NM, NT, 1, 1, 8, 8, WV>(a, tl, pre, e, 1, pos0, pos1, R, sp, n_split);
   } else {
-    if (cls == 0) stream_body<NM, NT, RT0, 2, B, B>(a, tl, pre, e, 0, pos0, pos1, R, sp, n_split);
-    else if (cls == 1) stream_body<NM, NT, 1, 2, 8, B>(a, tl, pre, e, 1, pos0, pos1, R, sp, n_split);
-    else if (cls == 2) stream_body<NM, NT, 1, 2, B, 8>(a, tl, pre, e, 2, pos0, pos1, R, sp, n_split);
-    else stream_body<NM, NT, 1, 2, 8, 8>(a, tl, pre, e, 3, pos0, pos1, R, sp, n_split);
+    if (!VEC && cls == 0) stream_body<NM, NT, 1, 2, B, B, WV>(a, tl, pre, e, 0, pos0, pos1, R, sp, n_split);
+    else if (cls == 1) stream_body<NM, NT, 1, 2, 8, B, WV>(a, tl, pre, e, 1, pos0, pos1, R, sp, n_split);
+    else if (cls == 2) stream_body<NM, NT, 1, 2, B, 8, WV>(a, tl, pre, e, 2, pos0, pos1, R, sp, n_split);
+    else stream_body<NM, NT, 1, 2, 8, 8, WV>(a, tl, pre, e, 3, pos0, pos1, R, sp, n_split);
   }
 }
 
@@ -483,29 +657,32 @@ __device__ __forceinline__ void block_variant(int l, int nblk, int m, int& blk, 
 // then the class-0 workgroups of the entries of the map (shared experts,
 // then routed experts widest first), each entry's row blocks sized by its
 // bit-width so that every workgroup streams about the same bytes.
-template <int NM, int NT, int NK>
-__global__ void __launch_bounds__(64 * kWavesOf<NK>) __attribute__((amdgpu_waves_per_eu(2)))
+template <int NM, int NT, int NK, bool VEC>
+__global__ void __launch_bounds__((64 * kWavesOf<NK, VEC>)) __attribute__((amdgpu_waves_per_eu(2)))
 ffn_stream_kernel(FfnArgs a, WgMap map) {
   __shared__ __attribute__((aligned(16))) XTile<NM, NT> tl;
-  constexpr int rows1 = kWavesOf<NK> * 16;   // rows of one row tile per wave
+  constexpr int WV = kWavesOf<NK, VEC>;
+  constexpr int rows1 = WV * 16;   // rows of one row tile per wave
   const int bid = blockIdx.x;
   const int n_swg = map.n_r * map.n_sw * map.m_r;
-  int e, blk, v;
+  int e, blk, v, B;
   const bool sw = bid < n_swg;
   if (sw) {
     const int per = map.n_sw * map.m_r;
     e = bid / per;
     block_variant(bid - e * per, map.n_sw, map.m_r, blk, v);
+    B = map.bits[e / 4] >> (8 * (e % 4)) & 0xFFu;
   } else {
-    const int w = bid - n_swg;
-    int lo = 0, hi = map.n_ent - 1;   // last entry whose start is <= w
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (map.ent_start[mid] <= w) lo = mid; else hi = mid - 1;
-    }
-    e = map.ent_e[lo];
-    const int m = e < a.E ? map.m_r : map.m_s;
-    block_variant(w - map.ent_start[lo], (map.ent_start[lo + 1] - map.ent_start[lo]) / m, m, blk, v);
+    const int per_s = map.blk_s * map.m_s, per_r = map.blk_r * map.m_r;
+    int w = bid - n_swg;
+    const bool shared = w < map.n_s * per_s;
+    if (!shared) w -= map.n_s * per_s;
+    const int i = w / (shared ? per_s : per_r);
+    block_variant(w - i * (shared ? per_s : per_r), shared ? map.blk_s : map.blk_r, shared ? map.m_s : map.m_r, blk,
+                  v);
+    const int ent = map.ent[shared ? i : map.n_s + i];
+    e = ent & 0xFFFF;
+    B = ent >> 16;
   }
   const bool routed = e < a.E;
   const int n_tt = routed ? map.tt_r : map.tt_s;
@@ -526,15 +703,19 @@ ffn_stream_kernel(FfnArgs a, WgMap map) {
     pre.code_off[kk] = a.kd[kind0 + kk].code_off[e];
     pre.sz_off[kk] = a.kd[kind0 + kk].sz_off[e];
   }
+  {  // class 0 starts at position 0: the wave's rows do not wait for the class sizes
+    const int pos = min(blk * rows1 + 16 * static_cast<int>(threadIdx.x >> 6) + static_cast<int>(threadIdx.x & 15), R - 1);
+    pre.row = pos;
+    if (routed && !sw) pre.row = (NK == 1 ? a.order_dn : a.order_gu)[static_cast<int64_t>(e) * R + pos];
+  }
   if (uni(o1) <= uni(o0)) return;
-  const int B = map.bits[e];
-  int cls = 0, start = 0, count = R, rows = rows1 * stream_rt(B);
+  int cls = 0, start = 0, count = R;
+  constexpr int rows = rows1;
   if (routed) {
 #pragma unroll
     for (int c = 0; c < 4; c++) cnt[c] = uni(cnt[c]);
     count = cnt[0];
     if (sw) {   // find the switched class of this workgroup
-      rows = rows1;
       start = cnt[0];
       cls = 4;
       for (int c = 1; c < (NK == 1 ? 2 : 4); c++) {
@@ -554,31 +735,46 @@ ffn_stream_kernel(FfnArgs a, WgMap map) {
   if (blk * rows >= count) return;
   const int pos1 = min(pos0 + rows, start + count);
   const int n_split = map.n_split;
+  if constexpr (VEC) {   // T <= kVecTok: no expert has more tokens
+    if (cls == 0) {
+      const int seg0 = uni(o0), n_tok = uni(o1) - seg0;
+      if (B == 8) vec_dispatch<NM, NK, 8>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, n_tok);
+      else if (NM == 2 && B == 16) {
+        if constexpr (NM == 2) vec_dispatch<NM, NK, 16>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, n_tok);
+      } else if (B == 4) vec_dispatch<NM, NK, 4>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, n_tok);
+      else if (B == 2) vec_dispatch<NM, NK, 2>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, n_tok);
+      else if constexpr (NM == 4) {
+        if (B == 6) vec_dispatch<NM, NK, 6>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, n_tok);
+        else vec_dispatch<NM, NK, 3>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, n_tok);
+      }
+      return;
+    }
+  }
   if constexpr (NT == 2) {
     // an expert with at most 16 tokens needs one 16-token tile: half the
     // contraction and epilogue work of the 32-token tile (same LDS)
     if (uni(o1) - uni(o0) <= 16) {
       auto& t1 = *reinterpret_cast<XTile<NM, 1>*>(&tl);
-      if (B == 8) dispatch_class<NM, 1, NK, 8>(a, t1, pre, e, cls, pos0, pos1, R, sp, n_split);
+      if (B == 8) dispatch_class<NM, 1, NK, 8, WV, VEC>(a, t1, pre, e, cls, pos0, pos1, R, sp, n_split);
       else if (NM == 2 && B == 16) {   // unquantized experts need group 64
-        if constexpr (NM == 2) dispatch_class<NM, 1, NK, 16>(a, t1, pre, e, cls, pos0, pos1, R, sp, n_split);
-      } else if (B == 4) dispatch_class<NM, 1, NK, 4>(a, t1, pre, e, cls, pos0, pos1, R, sp, n_split);
-      else if (B == 2) dispatch_class<NM, 1, NK, 2>(a, t1, pre, e, cls, pos0, pos1, R, sp, n_split);
+        if constexpr (NM == 2) dispatch_class<NM, 1, NK, 16, WV, VEC>(a, t1, pre, e, cls, pos0, pos1, R, sp, n_split);
+      } else if (B == 4) dispatch_class<NM, 1, NK, 4, WV, VEC>(a, t1, pre, e, cls, pos0, pos1, R, sp, n_split);
+      else if (B == 2) dispatch_class<NM, 1, NK, 2, WV, VEC>(a, t1, pre, e, cls, pos0, pos1, R, sp, n_split);
       else if constexpr (NM == 4) {
-        if (B == 6) dispatch_class<NM, 1, NK, 6>(a, t1, pre, e, cls, pos0, pos1, R, sp, n_split);
-        else dispatch_class<NM, 1, NK, 3>(a, t1, pre, e, cls, pos0, pos1, R, sp, n_split);
+        if (B == 6) dispatch_class<NM, 1, NK, 6, WV, VEC>(a, t1, pre, e, cls, pos0, pos1, R, sp, n_split);
+        else dispatch_class<NM, 1, NK, 3, WV, VEC>(a, t1, pre, e, cls, pos0, pos1, R, sp, n_split);
       }
       return;
     }
   }
-  if (B == 8) dispatch_class<NM, NT, NK, 8>(a, tl, pre, e, cls, pos0, pos1, R, sp, n_split);
+  if (B == 8) dispatch_class<NM, NT, NK, 8, WV, VEC>(a, tl, pre, e, cls, pos0, pos1, R, sp, n_split);
   else if (NM == 2 && B == 16) {   // unquantized experts need group 64
-    if constexpr (NM == 2) dispatch_class<NM, NT, NK, 16>(a, tl, pre, e, cls, pos0, pos1, R, sp, n_split);
-  } else if (B == 4) dispatch_class<NM, NT, NK, 4>(a, tl, pre, e, cls, pos0, pos1, R, sp, n_split);
-  else if (B == 2) dispatch_class<NM, NT, NK, 2>(a, tl, pre, e, cls, pos0, pos1, R, sp, n_split);
+    if constexpr (NM == 2) dispatch_class<NM, NT, NK, 16, WV, VEC>(a, tl, pre, e, cls, pos0, pos1, R, sp, n_split);
+  } else if (B == 4) dispatch_class<NM, NT, NK, 4, WV, VEC>(a, tl, pre, e, cls, pos0, pos1, R, sp, n_split);
+  else if (B == 2) dispatch_class<NM, NT, NK, 2, WV, VEC>(a, tl, pre, e, cls, pos0, pos1, R, sp, n_split);
   else if constexpr (NM == 4) {
-    if (B == 6) dispatch_class<NM, NT, NK, 6>(a, tl, pre, e, cls, pos0, pos1, R, sp, n_split);
-    else dispatch_class<NM, NT, NK, 3>(a, tl, pre, e, cls, pos0, pos1, R, sp, n_split);
+    if (B == 6) dispatch_class<NM, NT, NK, 6, WV, VEC>(a, tl, pre, e, cls, pos0, pos1, R, sp, n_split);
+    else dispatch_class<NM, NT, NK, 3, WV, VEC>(a, tl, pre, e, cls, pos0, pos1, R, sp, n_split);
   }
 }
 
@@ -586,16 +782,20 @@ ffn_stream_kernel(FfnArgs a, WgMap map) {
 // once per group size (MOE_FFN_NM = 2 or 4, that is 64 or 128) to spread the
 // work over several compiler processes.
 #if !defined(MOE_FFN_NM) || MOE_FFN_NM == 2
-template __global__ void ffn_stream_kernel<2, 1, 1>(FfnArgs, WgMap);
-template __global__ void ffn_stream_kernel<2, 1, 2>(FfnArgs, WgMap);
-template __global__ void ffn_stream_kernel<2, 2, 1>(FfnArgs, WgMap);
-template __global__ void ffn_stream_kernel<2, 2, 2>(FfnArgs, WgMap);
+template __global__ void ffn_stream_kernel<2, 1, 1, false>(FfnArgs, WgMap);
+template __global__ void ffn_stream_kernel<2, 1, 1, true>(FfnArgs, WgMap);
+template __global__ void ffn_stream_kernel<2, 1, 2, false>(FfnArgs, WgMap);
+template __global__ void ffn_stream_kernel<2, 1, 2, true>(FfnArgs, WgMap);
+template __global__ void ffn_stream_kernel<2, 2, 1, false>(FfnArgs, WgMap);
+template __global__ void ffn_stream_kernel<2, 2, 2, false>(FfnArgs, WgMap);
 #endif
 #if !defined(MOE_FFN_NM) || MOE_FFN_NM == 4
-template __global__ void ffn_stream_kernel<4, 1, 1>(FfnArgs, WgMap);
-template __global__ void ffn_stream_kernel<4, 1, 2>(FfnArgs, WgMap);
-template __global__ void ffn_stream_kernel<4, 2, 1>(FfnArgs, WgMap);
-template __global__ void ffn_stream_kernel<4, 2, 2>(FfnArgs, WgMap);
+template __global__ void ffn_stream_kernel<4, 1, 1, false>(FfnArgs, WgMap);
+template __global__ void ffn_stream_kernel<4, 1, 1, true>(FfnArgs, WgMap);
+template __global__ void ffn_stream_kernel<4, 1, 2, false>(FfnArgs, WgMap);
+template __global__ void ffn_stream_kernel<4, 1, 2, true>(FfnArgs, WgMap);
+template __global__ void ffn_stream_kernel<4, 2, 1, false>(FfnArgs, WgMap);
+template __global__ void ffn_stream_kernel<4, 2, 2, false>(FfnArgs, WgMap);
 #endif
 
 }  // namespace ffn

@@ -278,6 +278,52 @@ def test_routed_token_tiles_split_skewed(orc):
     assert err <= TOL and err <= DIAG_STREAM
 
 
+@pytest.mark.parametrize("T", [1, 2])
+@pytest.mark.parametrize("d,f,fs,bits", [
+    (128, 256, 128, (8, 6, 4, 3, 2, 4, 8, 2)),      # one group of K; a partial pass of 16
+    (2176, 1408, 2944, (2, 3, 4, 6, 8, 3, 6, 2)),   # 17 and 11 and 23 groups: a pass and a remainder
+    (4096, 2048, 256, (4, 8, 3, 2, 6, 4, 2, 8)),    # whole passes, two of them
+])
+def test_one_or_two_tokens(orc, T, d, f, fs, bits):
+    # batches without matrix tiles: every width, routed and shared experts,
+    # rows before and after a switch, split down projections
+    import dataclasses
+    import paper_2503_21135_amd as P
+    cfg = dataclasses.replace(mi.TINY6, name="vec", cfg_id=12, n_experts=8, n_shared=1, d_model=d,
+                              d_ff=f, d_ff_shared=fs, bits_literal=bits)
+    inp = mi.LayerInputs(cfg)
+    layer = P.MoELayer(inp)
+    x = mi.make_x(cfg, T, stream=980)
+    for mode in ("reset", "switched"):
+        if mode == "switched":
+            layer.set_epoch(0)
+        rs = oracle_row_slots(orc, inp) if mode == "switched" else None
+        for first in (0, 3, 6):     # experts `first` and `first` + 1 take the tokens
+            bias = np.zeros(8, np.float32)
+            bias[first:first + 2] = 50.0
+            y, b = _run(layer, x, bias)
+            res = orc.layer_forward(inp, x, bias=bias, row_slot=rs)
+            routing_matches(layer, res, b)
+            err = rel_l2(y, res["y"])
+            print("vec T", T, d, f, fs, mode, first, "rel_l2", err, flush=True)
+            assert err <= TOL and err <= DIAG_STREAM
+
+
+@pytest.mark.parametrize("T", [1, 2])
+def test_one_or_two_tokens_unquantized(orc, T):
+    # bf16 weights at group 64 (16 codes per lane)
+    import paper_2503_21135_amd as P
+    inp = mi.LayerInputs(mi.unquantized(mi.TINY))
+    layer = P.MoELayer(inp)
+    x = mi.make_x(inp.cfg, T, stream=981)
+    y, b = _run(layer, x)
+    res = orc.layer_forward(inp, x)
+    routing_matches(layer, res, b)
+    err = rel_l2(y, res["y"])
+    print("vec bf16 T", T, "rel_l2", err, flush=True)
+    assert err <= TOL and err <= DIAG_STREAM
+
+
 @pytest.mark.parametrize("T", [257, 260, 333, 388, 520])
 def test_tile_token_blocks(orc, T):
     # 65 to 130 tokens per expert on the tile kernel: last tiles of one to four
