@@ -173,8 +173,7 @@ def ffn_source_hash():
     return h.hexdigest()[:16]
 
 
-FFN_SOURCES = ("ffn.hip", "ffn_common.hpp", "ffn_prep.hip", "ffn_stream.hip", "ffn_tile.hip",
-               "common.hpp")
+FFN_SOURCES = ("ffn.hip", "ffn_common.hpp", "ffn_stream.hip", "ffn_tile.hip", "common.hpp")
 
 
 

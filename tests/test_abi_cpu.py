@@ -218,3 +218,10 @@ def test_code_row_words(lib):
     assert lib.moe_code_row_words(4096, 16) == 4096 // 2 + 32   # unquantized bf16 rows
     for K, b in ((4096, 5), (100, 4), (0, 4), (-128, 8), (4096, 12)):
         assert lib.moe_code_row_words(K, b) == 0
+
+
+def test_bench_hashes_the_ffn_sources():
+    import bench
+    csrc = os.path.join(ROOT, "paper_2503_21135_amd", "csrc")
+    assert set(bench.FFN_SOURCES) == {f for f in os.listdir(csrc) if f.startswith("ffn") and not f.endswith(".o")} | {"common.hpp"}
+    assert re.fullmatch("[0-9a-f]{16}", bench.ffn_source_hash())
