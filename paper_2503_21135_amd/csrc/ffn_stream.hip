@@ -655,8 +655,7 @@ __device__ __forceinline__ void block_variant(int l, int nblk, int m, int& blk, 
 // workgroups of the routed experts first (n_sw per expert, an upper bound on
 // what its copies can need; those past its actual class sizes exit at once),
 // then the class-0 workgroups of the entries of the map (shared experts,
-// then routed experts widest first), each entry's row blocks sized by its
-// bit-width so that every workgroup streams about the same bytes.
+// then routed experts widest first), as many row blocks per entry of a kind.
 template <int NM, int NT, int NK, bool VEC>
 __global__ void __launch_bounds__((64 * kWavesOf<NK, VEC>)) __attribute__((amdgpu_waves_per_eu(2)))
 ffn_stream_kernel(FfnArgs a, WgMap map) {
