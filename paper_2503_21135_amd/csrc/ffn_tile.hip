@@ -1,5 +1,6 @@
 // ffn_tile.hip -- the tile kernel of moe_expert_ffn_mixed, for experts with
-// many tokens (prefill sizes), and its work-plan kernel.
+// many tokens (prefill sizes), and the kernel that prepares its work plan and
+// activations.
 #include "ffn_common.hpp"
 
 namespace moe {
@@ -45,7 +46,7 @@ namespace ffn {
 // a wave's class picks its sources, so a small class costs one wave, not a
 // workgroup.  Work items (expert, row block, token tile; a down item also
 // takes a K slice and writes its own slice of o, which the combine adds) come
-// from a prefix table a small plan kernel builds from the routing offsets and
+// from a prefix table tile_prep_kernel builds from the routing offsets and
 // class counts, and are spread over a persistent grid so that the workgroups
 // of one XCD (hardware places workgroup b on XCD b % 8) take consecutive
 // items.  Within an expert the items run in super-tiles of kSuper row blocks
