@@ -496,10 +496,10 @@ __device__ __forceinline__ void wave_scatter_sum(float (&v)[NV], int lane) {
 }
 
 // The rows at order positions [pos0, pos1) of expert e on its base codes,
-// TT >= the expert's n_tok tokens, K groups [g0, g1) of split sp.
+// TT rows of its segment from seg0 on, K groups [g0, g1) of split sp.
 template <int NM, int NK, int B, int TT>
 __device__ __forceinline__ void vec_body(const FfnArgs& a, const Pre& pre, int e, int pos0, int pos1, int R, int sp,
-                                         int n_split, int seg0, int n_tok) {
+                                         int n_split, int seg0) {
   constexpr int g = NM * 32;
   constexpr int NW = kWords<NM, B>;
   constexpr int RB = NK * TT == 4 ? 8 : 16;   // rows whose sums a lane holds at once
@@ -531,7 +531,7 @@ __device__ __forceinline__ void vec_body(const FfnArgs& a, const Pre& pre, int e
   uint32_t xrow[TT];   // byte offset of the token's row
 #pragma unroll
   for (int t = 0; t < TT; t++) {
-    const int p = seg0 + min(t, n_tok - 1);
+    const int p = seg0 + t;
     xrow[t] = uni(static_cast<uint32_t>(2 * (down ? h_row(a, p) : static_cast<int64_t>(a.perm[p]) * K)));
   }
   uint32_t vm = kMagic, vh = kHighMagic<B, B>;
@@ -603,7 +603,7 @@ __device__ __forceinline__ void vec_body(const FfnArgs& a, const Pre& pre, int e
     const int v = lane / (kWave / N);
     const int r = rb + v / TT, t = v % TT;
     const int rid = __shfl(row, r & 15);
-    if (lane % (kWave / N) == 0 && r < n_rows && t < n_tok) {
+    if (lane % (kWave / N) == 0 && r < n_rows) {
       const int p = seg0 + t;
       if constexpr (down)
         a.o[static_cast<int64_t>(sp) * a.split_stride + static_cast<int64_t>(p) * R + rid] = acc[0][0];
@@ -613,11 +613,15 @@ __device__ __forceinline__ void vec_body(const FfnArgs& a, const Pre& pre, int e
   }
 }
 
+// The expert's segment two rows at a time.  Routing gives an expert at most
+// kVecTok rows of a batch this small, but a caller's own offsets may give it up
+// to T*k (a token that names an expert more than once).
 template <int NM, int NK, int B>
 __device__ __forceinline__ void vec_dispatch(const FfnArgs& a, const Pre& pre, int e, int pos0, int pos1, int R,
-                                             int sp, int n_split, int seg0, int n_tok) {
-  if (n_tok == 1) vec_body<NM, NK, B, 1>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, n_tok);
-  else vec_body<NM, NK, B, 2>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, n_tok);
+                                             int sp, int n_split, int seg0, int seg1) {
+#pragma nounroll
+  for (; seg1 - seg0 > 1; seg0 += 2) vec_body<NM, NK, B, 2>(a, pre, e, pos0, pos1, R, sp, n_split, seg0);
+  if (seg0 < seg1) vec_body<NM, NK, B, 1>(a, pre, e, pos0, pos1, R, sp, n_split, seg0);
 }
 
 
@@ -734,17 +738,17 @@ ffn_stream_kernel(FfnArgs a, WgMap map) {
   if (blk * rows >= count) return;
   const int pos1 = min(pos0 + rows, start + count);
   const int n_split = map.n_split;
-  if constexpr (VEC) {   // T <= kVecTok: no expert has more tokens
+  if constexpr (VEC) {
     if (cls == 0) {
-      const int seg0 = uni(o0), n_tok = uni(o1) - seg0;
-      if (B == 8) vec_dispatch<NM, NK, 8>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, n_tok);
+      const int seg0 = uni(o0), seg1 = uni(o1);
+      if (B == 8) vec_dispatch<NM, NK, 8>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, seg1);
       else if (NM == 2 && B == 16) {
-        if constexpr (NM == 2) vec_dispatch<NM, NK, 16>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, n_tok);
-      } else if (B == 4) vec_dispatch<NM, NK, 4>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, n_tok);
-      else if (B == 2) vec_dispatch<NM, NK, 2>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, n_tok);
+        if constexpr (NM == 2) vec_dispatch<NM, NK, 16>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, seg1);
+      } else if (B == 4) vec_dispatch<NM, NK, 4>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, seg1);
+      else if (B == 2) vec_dispatch<NM, NK, 2>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, seg1);
       else if constexpr (NM == 4) {
-        if (B == 6) vec_dispatch<NM, NK, 6>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, n_tok);
-        else vec_dispatch<NM, NK, 3>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, n_tok);
+        if (B == 6) vec_dispatch<NM, NK, 6>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, seg1);
+        else vec_dispatch<NM, NK, 3>(a, pre, e, pos0, pos1, R, sp, n_split, seg0, seg1);
       }
       return;
     }

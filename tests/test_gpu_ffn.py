@@ -309,6 +309,48 @@ def test_one_or_two_tokens(orc, T, d, f, fs, bits):
             assert err <= TOL and err <= DIAG_STREAM
 
 
+@pytest.mark.parametrize("loads,tokens", [
+    # rows of each expert; token of each row
+    ((0, 3, 1, 0, 2, 0, 0, 0), (0,) * 6),                                   # one token
+    ((5, 0, 3, 1, 0, 0, 2, 1), (0, 1, 1, 0, 1, 1, 0, 1, 0, 0, 1, 1)),       # two
+    ((0, 0, 0, 0, 0, 6, 0, 0), (0,) * 6),
+    ((0, 0, 0, 12, 0, 0, 0, 0), (1, 0) * 6),
+])
+@pytest.mark.parametrize("group", [64, 128])
+def test_one_or_two_tokens_own_offsets(orc, group, loads, tokens):
+    # a caller's own segments, in which a token names an expert more than once:
+    # an expert then has more rows than the batch has tokens
+    import dataclasses
+    import paper_2503_21135_amd as P
+    bits = (8, 6, 4, 3, 2, 4, 8, 2) if group == 128 else (8, 4, 4, 8, 2, 4, 8, 2)
+    k = 6
+    cfg = dataclasses.replace(mi.TINY6, name="own-offsets", cfg_id=13, n_experts=8, n_shared=1, top_k=k,
+                              d_model=256, d_ff=384, d_ff_shared=128, group=group, bits_literal=bits)
+    T = len(tokens) // k
+    inp = mi.LayerInputs(cfg)
+    layer = P.MoELayer(inp)
+    layer.set_epoch(0)
+    rs = oracle_row_slots(orc, inp)
+    x = mi.make_x(cfg, T, stream=982)
+    perm = np.array(tokens + tuple(range(T)), np.int32)
+    offsets = np.concatenate([[0], np.cumsum(loads + (T,))]).astype(np.int32)
+    n_split, nb = P.api.moe_ffn_plan(layer.desc, T, k)
+    o = torch.full((n_split, len(perm), cfg.d_model), float("nan"), device=dev())
+    ws = torch.empty(nb, dtype=torch.uint8, device=dev())
+    P.api.moe_expert_ffn_mixed(layer.desc, to_dev_bf16(x), k, torch.from_numpy(offsets).to(dev()),
+                               torch.from_numpy(perm).to(dev()), o, ws)
+    got = o.double().sum(0).cpu().numpy()
+    for e in range(9):
+        rows = perm[offsets[e]:offsets[e + 1]]
+        if len(rows) == 0:
+            continue
+        sw = [np.nonzero(rs[kind][e] >= 0)[0] if e < 8 else None for kind in range(3)]
+        W = [orc.effective_weight(inp.weight(e, kind), int(inp.bits[e]), group, sw[kind]) for kind in range(3)]
+        err = rel_l2(got[offsets[e]:offsets[e + 1]], orc.expert_ffn(*W, x, rows))
+        print("own offsets g", group, "expert", e, "rows", len(rows), "rel_l2", err, flush=True)
+        assert err <= DIAG_STREAM     # NaN (a row left out) fails
+
+
 @pytest.mark.parametrize("T", [1, 2])
 def test_one_or_two_tokens_unquantized(orc, T):
     # bf16 weights at group 64 (16 codes per lane)
