@@ -9,6 +9,8 @@
 // word layout are defined in moe_quant.h; parameter math is binary64, which
 // gfx950 rounds exactly as IEEE requires, so the codes are reproducible bit
 // for bit on any IEEE host.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace moe {
@@ -110,6 +112,21 @@ int pack_rows(int64_t n, int64_t K) {
   return rpw;
 }
 
+// The tiles go over a one-dimensional grid, row blocks innermost: its other
+// dimensions hold at most 65535 blocks, fewer than the widest rows have column
+// tiles.  A grid holds fewer than 2^32 threads.
+constexpr int64_t kPackMaxBlocks = (int64_t{1} << 24) - 1;
+
+struct PackTile {
+  int row, col;   // row block, column tile
+};
+
+__device__ __forceinline__ PackTile pack_tile(int n, int rpw) {
+  const int row_blocks = (n - 1) / rpw + 1;
+  const int col = blockIdx.x / row_blocks;
+  return PackTile{static_cast<int>(blockIdx.x) - col * row_blocks, col};
+}
+
 // Quantize and pack rpw list rows x up to kPackCols columns per workgroup.
 // Bound by the fp32 reads.  The tile's 8-weight items run over the threads row
 // after row (a row of K columns holds a whole number of groups, so a group is
@@ -132,9 +149,10 @@ pack_kernel(const float* __restrict__ w, int64_t ld_w, int K, const int32_t* __r
   constexpr int qmax = (1 << (B & 15)) - 1;
   __shared__ uint32_t szl[kGroups][kPackRows];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int c0 = blockIdx.y * kPackCols;
+  const PackTile tile = pack_tile(n, rpw);
+  const int c0 = tile.col * kPackCols;
   const int c8 = min(kPackCols, K - c0) / 8;   // items per row of the tile
-  const int i0 = blockIdx.x * rpw;
+  const int i0 = tile.row * rpw;
   const int nr = min(rpw, n - i0);
   auto load = [&](float (&v)[8], int it) {
     const bool on = it < nr * c8;   // the same for all lanes of a group
@@ -234,7 +252,7 @@ pack_kernel(const float* __restrict__ w, int64_t ld_w, int K, const int32_t* __r
   }
   __syncthreads();
   for (int t = tid; t < kGroups * kPackRows; t += 256) {
-    const int j = blockIdx.y * kGroups + t / kPackRows, i = t % kPackRows;
+    const int j = tile.col * kGroups + t / kPackRows, i = t % kPackRows;
     if (j < K / GR && i < nr) sz[static_cast<int64_t>(i0 + i) * sz_rs + static_cast<int64_t>(j) * sz_gs] = szl[t / kPackRows][i];
   }
 }
@@ -268,9 +286,10 @@ requant_kernel(const uint16_t* __restrict__ cache, int64_t ld_cache, int K,
   __shared__ uint32_t szl[kPackRows][kGroups];
   __shared__ int32_t bit_of[kPackRows];   // precision of each slot's expert, 0: left alone
   const int tid = threadIdx.x;
-  const int c0 = blockIdx.y * kPackCols;
+  const PackTile tile = pack_tile(n_slots, rpw);
+  const int c0 = tile.col * kPackCols;
   const int c8 = min(kPackCols, K - c0) / 8;   // items per row of the tile
-  const int s0 = blockIdx.x * rpw;
+  const int s0 = tile.row * rpw;
   const int ns = min(rpw, n_slots - s0);
   const int G = K / GR;
   if (tid < ns) bit_of[tid] = eb.b[hdr[2 * (s0 + tid)]];
@@ -328,7 +347,7 @@ requant_kernel(const uint16_t* __restrict__ cache, int64_t ld_cache, int K,
   }
   __syncthreads();
   for (int t = tid; t < kGroups * ns; t += 256) {
-    const int i = t / kGroups, j = blockIdx.y * kGroups + t % kGroups;
+    const int i = t / kGroups, j = tile.col * kGroups + t % kGroups;
     if (j < G && bit_of[i] != 0) sz[static_cast<int64_t>(s0 + i) * G + j] = szl[i][t % kGroups];
   }
 }
@@ -353,9 +372,13 @@ extern "C" int moe_quant_pack(const float* w, int64_t ld_w, int32_t R, int32_t K
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int rpw = pack_rows(n, K);
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(cdiv(n, rpw)), static_cast<unsigned>(cdiv(K, kPackCols))),
-                       dim3(256), 0, s, w, ld_w, K, rows, n, rpw, codes, ld_codes, sz, sz_row_stride, sz_group_stride,
-                       status);
+    const int64_t cols = cdiv(K, kPackCols), step = kPackMaxBlocks / cols * rpw;   // list rows of a launch
+    for (int64_t i = 0; i < n; i += step) {
+      const int m = static_cast<int>(std::min(step, n - i));
+      hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(cdiv(m, rpw) * cols)), dim3(256), 0, s,
+                         rows ? w : w + i * ld_w, ld_w, K, rows ? rows + i : rows, m, rpw, codes + i * ld_codes,
+                         ld_codes, sz + i * sz_row_stride, sz_row_stride, sz_group_stride, status);
+    }
   };
   if (group == 64) {
     switch (bits) {
@@ -406,8 +429,7 @@ extern "C" int moe_requant_channels(moe_layer_t* L, int32_t kind, const uint16_t
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int rpw = pack_rows(D.n_slots, K);
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(cdiv(D.n_slots, rpw)), static_cast<unsigned>(cdiv(K, kPackCols))),
-                       dim3(256), 0, s, cache, ld_cache, K, D.copy_hdr, D.n_slots, rpw, eb,
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(cdiv(D.n_slots, rpw) * cdiv(K, kPackCols))), dim3(256), 0, s, cache, ld_cache, K, D.copy_hdr, D.n_slots, rpw, eb,
                        const_cast<uint32_t*>(D.copy_codes), code_row_words(K, 8), const_cast<uint32_t*>(D.copy_sz),
                        status);
   };

@@ -121,3 +121,37 @@ def test_pack_tile_edges_and_ties(orc, bits, group, R, K):
     assert s == 0
     assert np.array_equal(codes, orc.pack(q, bits))
     assert np.array_equal(sz, orc.sz_words(s16, z16))
+
+
+def _periodic_pack_matches(R, K, bits, rows=None):
+    """Packs R weight rows of 64 columns repeated along K (and, with `rows`,
+    listed over and over) and compares every word with the small matrix's."""
+    import paper_2503_21135_amd as P
+    group = 64
+    small = torch.randn(R, group, device=dev()) * 0.02
+    words = group * bits // 32
+    c1 = torch.zeros(R, words, dtype=torch.int32, device=dev())
+    s1 = torch.zeros(R, dtype=torch.int32, device=dev())
+    P.moe_quant_pack(small, bits, group, c1, s1)
+    w = small.repeat(1, K // group)
+    n = R if rows is None else rows.numel()
+    codes = torch.zeros(n, K * bits // 32, dtype=torch.int32, device=dev())
+    sz = torch.zeros(n, K // group, dtype=torch.int32, device=dev())
+    P.moe_quant_pack(w, bits, group, codes, sz, rows=rows)
+    step = 1 << 24    # rows of a comparison
+    for i in range(0, n, step):
+        r = torch.arange(R, device=dev()) if rows is None else rows[i:i + step].long()
+        assert torch.equal(codes[i:i + step].view(len(r), -1, words), c1[r][:, None].expand(-1, K // group, -1))
+        assert torch.equal(sz[i:i + step], s1[r][:, None].expand(-1, K // group))
+
+
+def test_pack_row_wider_than_a_grid_dimension():
+    # more column tiles of 2048 than a grid's second dimension holds (65535)
+    _periodic_pack_matches(2, 2048 * 65536 + 64, 2)
+
+
+def test_pack_row_list_longer_than_a_grid():
+    # narrow rows, 16 of them per workgroup: more than 2^32 threads
+    n = (1 << 28) + 1000
+    rows = torch.arange(n, dtype=torch.int32, device=dev()).remainder_(7)
+    _periodic_pack_matches(7, 64, 2, rows)
