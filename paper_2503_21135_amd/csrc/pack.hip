@@ -263,7 +263,9 @@ struct ExpertBits {
   uint8_t b[MOE_MAX_EXPERTS];
 };
 
+// words of any 4-byte alignment (all that is asked of the cache and of copy_codes)
 typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2a4 __attribute__((ext_vector_type(2), aligned(4)));
 
 // Requantize rpw copy slots x up to kPackCols columns per workgroup, in
 // pack_kernel's shape: a lane takes 8 consecutive binary16 values of the
@@ -332,7 +334,7 @@ requant_kernel(const uint16_t* __restrict__ cache, int64_t ld_cache, int K,
 #pragma unroll
     for (int l = 0; l < 8; l++) o[l / 4] |= q[l] << hs_pos(l % 4, 8);
     if (!on) return;
-    *reinterpret_cast<u32x2*>(codes + static_cast<int64_t>(s0 + i) * ld_codes + (c0 + lc) / 4) = o;
+    *reinterpret_cast<u32x2a4*>(codes + static_cast<int64_t>(s0 + i) * ld_codes + (c0 + lc) / 4) = o;
     if (lc % GR == 0) {
       szl[i][lc / GR] = sc.sb | (fp16_of_small_int(sc.z) << 16);
       if (sc.sb == 0x7C00u && status) *status = MOE_ERR_RANGE;

@@ -96,3 +96,48 @@ def test_requant_mixtral_long_rows_bitexact(orc):
     wk, inp, layer = _layer("mixtral-decode")
     eb = inp.dataset_bits(0)
     _requant_and_check(orc, inp, layer, eb, kinds=(2, 0))
+
+
+@pytest.mark.parametrize("group", [64, 128])
+@pytest.mark.parametrize("n,K", [(37, 2176), (8195, 2176), (16389, 128)])
+def test_requant_tile_edges_and_ties(orc, group, n, K):
+    """Slot and column remainders of the requantization tile (2 to 16 slots x
+    2048 columns), every width, an expert left out between the others, cache
+    rows and copies that are 4-byte aligned only, and values whose quotient by
+    the scale is a half integer or next to one on the binary16 grid."""
+    import paper_2503_21135_amd as P
+    from paper_2503_21135_amd._lib import LayerDesc
+    rng = np.random.default_rng([group, n, K])
+    eb = np.array([2, 3, 0, 4, 6, 8], np.int32)
+    hdr = np.stack([rng.integers(0, 6, n), np.arange(n)], 1).astype(np.int32)
+    qmax = (1 << np.maximum(eb, 1)[hdr[:, 0]]) - 1
+    scale = np.array([2.0 ** -7, 3 * 2.0 ** -9, 5 * 2.0 ** -10])[rng.integers(0, 3, n)]
+    half = ((np.floor(rng.random((n, K)) * qmax[:, None]) + 0.5) * scale[:, None]).astype(np.float16)
+    off = rng.integers(-1, 2, (n, K))
+    v = np.where(off < 0, np.nextafter(half, np.float16(0)), np.where(off > 0, np.nextafter(half, np.float16(9)), half))
+    v[:, ::group] = 0.0                                          # every group spans [0, qmax] steps of the scale
+    v[:, 1::group] = (qmax * scale)[:, None]
+    v *= rng.choice(np.array([-1, 1], np.float16), (n, 1))
+    ld, rw = K + 6, P.api.moe_code_row_words(K, 8)
+    buf = torch.zeros(n * ld + 2, dtype=torch.float16, device="cuda")
+    cache = buf[2:].view(n, ld)[:, :K]
+    cache.copy_(torch.from_numpy(v))
+    codes = torch.full((n * rw + 1,), 0x5A5A5A5A, dtype=torch.int32, device="cuda")[1:]
+    sz = torch.full((n, K // group), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    dhdr = torch.from_numpy(hdr).cuda()
+    desc = LayerDesc()
+    desc.n_experts, desc.d_model, desc.d_ff, desc.group = 6, K, K, group
+    kd = desc.kind[0]
+    kd.n_slots, kd.copy_codes, kd.copy_sz = n, codes.data_ptr(), sz.data_ptr()
+    kd.copy_hdr, kd.copy_hdr_host = dhdr.data_ptr(), hdr.ctypes.data
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    P.api.moe_requant_channels(desc, 0, cache, eb, status=status)
+    assert int(status.item()) == 0
+    st, touched, q, s16, z16 = orc.requant_channels(v.view(np.uint16), hdr, eb, group)
+    assert st == orc.OK
+    want = np.full((n, rw), 0x5A5A5A5A, np.uint32)
+    want_sz = np.full((n, K // group), 0x5A5A5A5A, np.uint32)
+    want[touched, :K // 4] = orc.pack(q[touched], 8)
+    want_sz[touched] = orc.sz_words(s16[touched], z16[touched])
+    assert np.array_equal(codes.cpu().numpy().view(np.uint32).reshape(n, rw), want)
+    assert np.array_equal(sz.cpu().numpy().view(np.uint32), want_sz)
