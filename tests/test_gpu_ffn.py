@@ -309,6 +309,36 @@ def test_one_or_two_tokens(orc, T, d, f, fs, bits):
             assert err <= TOL and err <= DIAG_STREAM
 
 
+@pytest.mark.parametrize("T", [1, 2])
+@pytest.mark.parametrize("d,f,fs,bits", [
+    (128, 256, 128, (8, 4, 2, 4, 2, 8, 8, 2)),      # two groups of K
+    (2176, 1408, 2944, (2, 4, 8, 8, 4, 2, 4, 2)),   # 34, 22 and 46 groups: passes of 16 and a remainder
+    (4096, 2048, 256, (4, 8, 2, 8, 2, 4, 2, 8)),    # whole passes, four and two of them
+])
+def test_one_or_two_tokens_group64(orc, T, d, f, fs, bits):
+    # packed weights at group 64, rows before and after a switch
+    import dataclasses
+    import paper_2503_21135_amd as P
+    cfg = dataclasses.replace(mi.TINY6, name="vec64", cfg_id=14, n_experts=8, n_shared=1, d_model=d,
+                              d_ff=f, d_ff_shared=fs, group=64, bits_literal=bits)
+    inp = mi.LayerInputs(cfg)
+    layer = P.MoELayer(inp)
+    x = mi.make_x(cfg, T, stream=983)
+    for mode in ("reset", "switched"):
+        if mode == "switched":
+            layer.set_epoch(0)
+        rs = oracle_row_slots(orc, inp) if mode == "switched" else None
+        for first in (0, 2, 4, 6):     # experts `first` and `first` + 1 take the tokens
+            bias = np.zeros(8, np.float32)
+            bias[first:first + 2] = 50.0
+            y, b = _run(layer, x, bias)
+            res = orc.layer_forward(inp, x, bias=bias, row_slot=rs)
+            routing_matches(layer, res, b)
+            err = rel_l2(y, res["y"])
+            print("vec g64 T", T, d, f, fs, mode, first, "rel_l2", err, flush=True)
+            assert err <= TOL and err <= DIAG_STREAM
+
+
 @pytest.mark.parametrize("loads,tokens", [
     # rows of each expert; token of each row
     ((0, 3, 1, 0, 2, 0, 0, 0), (0,) * 6),                                   # one token
