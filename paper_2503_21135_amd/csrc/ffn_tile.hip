@@ -91,15 +91,15 @@ __device__ __forceinline__ u32x4* stage_of(const TileLds& l, int b) { return b =
 // Waves of expert e: class c of its row order (routed experts; a shared
 // expert is one class of R rows) takes ceil(count / kTileWaveRows) waves,
 // classes in order.  pre[c] = first wave of class c (pre[NC] = the total),
-// beg[c] / cnt[c] = its positions.  UNI: e is the same in every lane (the
-// counts then go through readfirstlane, so they are scalar values).
+// beg[c] / cnt[c] = its positions.  e is the same in every lane; the counts go
+// through readfirstlane, so they are scalar values.
 template <int NK>
 struct TileWaves {
   static constexpr int NC = NK == 1 ? 2 : 4;
   int pre[NC + 1], beg[NC], cnt[NC];
 };
 
-template <int NK, bool UNI>
+template <int NK>
 __device__ __forceinline__ TileWaves<NK> tile_waves(const FfnArgs& a, int e, int R) {
   constexpr int NC = TileWaves<NK>::NC;
   TileWaves<NK> w;
@@ -107,8 +107,7 @@ __device__ __forceinline__ TileWaves<NK> tile_waves(const FfnArgs& a, int e, int
   int start = 0;
 #pragma unroll
   for (int c = 0; c < NC; c++) {
-    int cn = e < a.E ? a.class_cnt[(NK == 1 ? 4 * a.E : 0) + 4 * e + c] : (c == 0 ? R : 0);
-    if constexpr (UNI) cn = uni(cn);
+    const int cn = uni(e < a.E ? a.class_cnt[(NK == 1 ? 4 * a.E : 0) + 4 * e + c] : (c == 0 ? R : 0));
     w.beg[c] = start;
     w.cnt[c] = cn;
     w.pre[c + 1] = w.pre[c] + (cn + kTileWaveRows<NK> - 1) / kTileWaveRows<NK>;
@@ -117,20 +116,23 @@ __device__ __forceinline__ TileWaves<NK> tile_waves(const FfnArgs& a, int e, int
   return w;
 }
 
-// Items of expert map.e0 + i of one stage: (row blocks of eight waves) x
-// (token tiles) x (K slices).
+// Row blocks (of eight waves) of an expert whose classes have cnt[c] rows.
 template <int NK>
-__device__ __forceinline__ int tile_items(const FfnArgs& a, int e, int tiles, int n_split) {
-  const TileWaves<NK> w = tile_waves<NK, false>(a, e, NK == 1 ? a.d : (e < a.E ? a.f : a.fs));
-  return tiles * ((w.pre[TileWaves<NK>::NC] + kTileWaves - 1) / kTileWaves) * n_split;
+__device__ __forceinline__ int tile_row_blocks(const int (&cnt)[TileWaves<NK>::NC]) {
+  int waves = 0;
+#pragma unroll
+  for (int c = 0; c < TileWaves<NK>::NC; c++) waves += (cnt[c] + kTileWaveRows<NK> - 1) / kTileWaveRows<NK>;
+  return (waves + kTileWaves - 1) / kTileWaves;
 }
 
-// Relative cost of an expert's items: the 32-token blocks of its largest token
-// tile, then the width (one-width layers at 4096 tokens run at 1183 / 1090 /
-// 956 / 947 / 875 TFLOP/s at 2 / 4 / 8 / 3 / 6 bits).
-__device__ __forceinline__ int tile_cost(int n_tok, int bits) {
+// Relative cost of an expert's items of one stage: the 32-token blocks of its
+// largest token tile, then the width (one-width layers at 4096 tokens run at
+// 1183 / 1090 / 956 / 947 / 875 TFLOP/s at 2 / 4 / 8 / 3 / 6 bits), over the K
+// columns of the expert (the down items of a wide shared expert are several times
+// as long as the routed experts').  At most 86 * 2^24: validate_layer bounds K.
+__device__ __forceinline__ int tile_cost(int n_tok, int bits, int K) {
   const int blocks = (min(n_tok, kTileTok) + 31) / 32;
-  return 16 * blocks + (bits == 2 ? 0 : bits == 4 ? 5 : bits == 6 ? 22 : 16);
+  return (16 * blocks + (bits == 2 ? 0 : bits == 4 ? 5 : bits == 6 ? 22 : 16)) * K;
 }
 
 #if !defined(MOE_FFN_NM) || MOE_FFN_NM == 2   // one copy of the kernel that is no template
@@ -162,39 +164,62 @@ __device__ __forceinline__ void gather_f16(const FfnArgs& a, int T) {
 
 // Blocks [0, gridDim.x - 1): the fp16 copy of the T token rows.  Last block:
 // the work plan of both stages, plan[stage] = {prefix[0 .. n_e], order[0 ..
-// n_e)} (stage 0 gate/up, 1 down): the launch's experts by falling item cost
-// and the exclusive prefix of their items in that order, so that the items
-// handed out last, which end the launch, are the short ones; and the hand-out
-// counters of both stages, zeroed.
+// n_e)} (stage 0 gate/up, 1 down): the launch's experts by falling item cost of
+// the stage and the exclusive prefix of their items in that order, so that the
+// items handed out last, which end the launch, are the short ones; and the
+// hand-out counters of both stages, zeroed.
 __global__ void __launch_bounds__(256) tile_prep_kernel(FfnArgs a, TileMap map, int T, int32_t* __restrict__ plan) {
   if (blockIdx.x + 1 < gridDim.x) {
     gather_f16(a, T);
     return;
   }
-  __shared__ int key[MOE_MAX_EXPERTS], sorted[2][MOE_MAX_EXPERTS], wave_sum[2][4];
+  __shared__ int key[2][MOE_MAX_EXPERTS], sorted[2][MOE_MAX_EXPERTS], wave_sum[2][4];
   const int i = threadIdx.x, lane = i & 63, wv = i >> 6;
   const int e = map.e0 + i;
   if (i < 2) plan[(i + 1) * kTilePlanInts - 1] = 0;   // the stage's hand-out counter
-  int items[2] = {0, 0}, my_key = -1;
+  int items[2] = {0, 0}, cost[2] = {-1, -1};
   if (i < map.n_e) {
+    // class sizes loaded for every expert, shared ones too (an expert's in
+    // range): a branch around a load would wait for each of them in turn
+    const bool routed = e < a.E;
+    const int32_t* cc = a.class_cnt + 4 * min(e, a.E - 1);
+    int gu[4], dn[2];
+#pragma unroll
+    for (int c = 0; c < 4; c++) gu[c] = cc[c];
+#pragma unroll
+    for (int c = 0; c < 2; c++) dn[c] = cc[4 * a.E + c];
     const int n_tok = a.offsets[e + 1] - a.offsets[e];
+#pragma unroll
+    for (int c = 0; c < 4; c++) gu[c] = routed ? gu[c] : (c == 0 ? a.fs : 0);
+#pragma unroll
+    for (int c = 0; c < 2; c++) dn[c] = routed ? dn[c] : (c == 0 ? a.d : 0);
+    // items: (row blocks) x (token tiles) x (K slices)
     const int tiles = (n_tok + kTileTok - 1) / kTileTok;
-    items[0] = tile_items<2>(a, e, tiles, 1);
-    items[1] = tile_items<1>(a, e, tiles, map.n_split);
-    my_key = tile_cost(n_tok, map.bits[i]);
+    items[0] = tiles * tile_row_blocks<2>(gu);
+    items[1] = tiles * tile_row_blocks<1>(dn) * map.n_split;
+    cost[0] = tile_cost(n_tok, map.bits[i], a.d);
+    cost[1] = tile_cost(n_tok, map.bits[i], routed ? a.f : a.fs);
   }
-  key[i] = my_key;
+#pragma unroll
+  for (int st = 0; st < 2; st++) key[st][i] = cost[st];
   __syncthreads();
-  int rank = 0;
-  for (int j = 0; j < map.n_e; j++) rank += (key[j] > my_key || (key[j] == my_key && j < i)) ? 1 : 0;
+  int rank[2] = {0, 0};
+  static_assert(MOE_MAX_EXPERTS == 256, "one thread per expert; keys past n_e are -1");
+#pragma unroll 8
+  for (int j = 0; j < (map.n_e + 7) / 8 * 8; j++)
+#pragma unroll
+    for (int st = 0; st < 2; st++)
+      rank[st] += (key[st][j] > cost[st] || (key[st][j] == cost[st] && j < i)) ? 1 : 0;
   if (i < map.n_e) {
+#pragma unroll
     for (int st = 0; st < 2; st++) {
-      sorted[st][rank] = items[st];
-      plan[st * kTilePlanInts + MOE_MAX_EXPERTS + 1 + rank] = i;
+      sorted[st][rank[st]] = items[st];
+      plan[st * kTilePlanInts + MOE_MAX_EXPERTS + 1 + rank[st]] = i;
     }
   }
   __syncthreads();
   int incl[2], own[2];
+#pragma unroll
   for (int st = 0; st < 2; st++) {
     own[st] = incl[st] = i < map.n_e ? sorted[st][i] : 0;
 #pragma unroll
@@ -205,6 +230,7 @@ __global__ void __launch_bounds__(256) tile_prep_kernel(FfnArgs a, TileMap map, 
     if (lane == kWave - 1) wave_sum[st][wv] = incl[st];
   }
   __syncthreads();
+#pragma unroll
   for (int st = 0; st < 2; st++) {
     int before = 0;
     for (int w = 0; w < wv; w++) before += wave_sum[st][w];
@@ -651,8 +677,17 @@ ffn_tile_kernel(FfnArgs a, TileMap map, const int32_t* __restrict__ plan, int32_
   // waited for the slowest one (with 96-token tiles and costly items first,
   // fixed -> handed out: Mixtral-shaped layer at 333 tokens, 1.8 rounds, gate/up
   // 279 -> 271 us, down 184 -> 177; at 4096 tokens, 15 rounds, the whole call
-  // 3.00 -> 2.86 ms).
-  const int n_fixed = max(total / G - 1, 0);
+  // 3.00 -> 2.86 ms).  Where the items contract different lengths of K (down, a
+  // shared expert wider than the routed ones beside them) all are handed out,
+  // the long ones first: a workgroup with a long item does not get a fixed share
+  // of the short ones too.  Qwen-shaped layer (44 against 11 groups), whole calls
+  // in us with the shared expert placed by width alone / first / first and all
+  // handed out: 2048 tokens 504 / 482 / 473 at 8 bits, 531 / 502 / 489 at 6, 470 /
+  // 470 / 456 at 4, 461 / 472 / 459 mixed; 4096 tokens 806 / 791 / 789, 842 / 833 /
+  // 831, 756 / 754 / 750, 751 / 748 / 753 (the loss of L2 sharing: at equal lengths,
+  // DeepSeek-shaped layer at 8192 tokens, it costs 1526 -> 1538).
+  const bool equal_k = NK == 2 || a.f == a.fs || map.n_e <= a.E;
+  const int n_fixed = equal_k ? max(total / G - 1, 0) : 0;
   for (int it = 0;; it++) {
     int item;
     if (it < n_fixed) {
@@ -675,7 +710,7 @@ ffn_tile_kernel(FfnArgs a, TileMap map, const int32_t* __restrict__ plan, int32_
     const bool routed = e < a.E;
     const int R = NK == 1 ? a.d : (routed ? a.f : a.fs);
     // the expert's waves, class after class; eight waves per row block
-    const TileWaves<NK> w = tile_waves<NK, true>(a, e, R);
+    const TileWaves<NK> w = tile_waves<NK>(a, e, R);
     constexpr int NC = TileWaves<NK>::NC;
     const int n_w = w.pre[NC];
     const int n_rb = (n_w + kTileWaves - 1) / kTileWaves;

@@ -423,6 +423,41 @@ def test_tile_token_blocks(orc, T):
     assert np.array_equal(y.view(np.uint32), again.view(np.uint32))
 
 
+@pytest.mark.parametrize("bits", [8, 6, 3, 2])
+def test_tile_plan_long_items_first(bits):
+    # the tile kernel's plan (in the workspace, after the hidden activations):
+    # per stage an order of the experts and the prefix of their items.  The
+    # down items of a shared expert with 4 times the routed experts' d_ff are
+    # the longest of the launch and come first; at equal K and width, experts of
+    # more 32-token blocks do
+    import dataclasses
+    import paper_2503_21135_amd as P
+    cfg = dataclasses.replace(mi.TINY6, name="plan", cfg_id=15, n_shared=2, d_ff=256, d_ff_shared=1024,
+                              bits_literal=(bits,) * 8)
+    inp = mi.LayerInputs(cfg)
+    layer = P.MoELayer(inp)
+    layer.set_epoch(0)
+    T, k, E, S = 520, cfg.top_k, 8, 2
+    _, b = _run(layer, mi.make_x(cfg, T, stream=984), np.linspace(-0.3, 0.3, 8).astype(np.float32))
+    n_tok = np.diff(b.offsets.cpu().numpy())
+    ws = b.ffn_ws
+    at = -ws.data_ptr() % 256 + (2 * (T * k * cfg.d_ff + S * T * cfg.d_ff_shared) + 255) // 256 * 256
+    plan = ws[at:at + 2 * 2 * 257 * 4].view(torch.int32).cpu().numpy().reshape(2, 2 * 257)
+    cnt = layer.class_cnt.cpu().numpy().reshape(2, E, 4)
+    for stage, (rows, slices) in enumerate(((32, 1), (64, b.n_split))):
+        order, prefix = plan[stage, 257:257 + E + S], plan[stage, :E + S + 1]
+        assert sorted(order) == list(range(E + S))
+        for i, e in enumerate(order):
+            c = cnt[stage, e] if e < E else np.array([cfg.d_ff_shared if stage == 0 else cfg.d_model])
+            blocks = -(-int((-(-c // rows)).sum()) // 8)
+            assert prefix[i + 1] - prefix[i] == -(-n_tok[e] // 128) * blocks * slices
+        tok_blocks = [-(-min(n_tok[e], 128) // 32) for e in order if e < E]
+        assert tok_blocks == sorted(tok_blocks, reverse=True)
+        if stage == 1:
+            assert list(order[:S]) == [E, E + 1]
+    assert len(set(tok_blocks)) > 1
+
+
 def test_tile_sets_with_split_k(orc):
     # 4 routed experts (8/4/6/2-bit) + 1 shared, d_ff = 2048, 64 tokens: the
     # routed experts expect 32 tokens and the shared one sees 64, so both
