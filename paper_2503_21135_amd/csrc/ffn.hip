@@ -23,7 +23,7 @@ struct Plan {
   int nt_routed, nt_shared;   // token tiles of the streaming kernel, 0: tile kernel
   bool vec;                   // the streaming kernel's form for batches of one or two tokens
   int tt_routed, tt_shared;   // workgroup sets per row block, each taking every n-th 32-token tile
-  size_t reserved[2], h_bytes, tile_bytes, x16_bytes, total;
+  size_t h_bytes, tile_bytes, x16_bytes, total;
 };
 
 // Shared experts with up to this many tokens stream, one workgroup set per
@@ -76,10 +76,8 @@ Plan make_plan(const moe_layer_t* L, int T, int k) {
   Plan p{};
   const int E = L->n_experts, S = L->n_shared, g = L->group;
   const int64_t Tk = static_cast<int64_t>(T) * k;
-  const int64_t rows = static_cast<int64_t>(T) * (k + S);
   const int64_t base_waves = static_cast<int64_t>(E + S) * (L->d_model / 32);
   const int fmin = S > 0 ? std::min(L->d_ff, L->d_ff_shared) : L->d_ff;
-  const int fmax = S > 0 ? std::max(L->d_ff, L->d_ff_shared) : L->d_ff;
   const int gmin = fmin / g;
   int ns = static_cast<int>(cdiv(4096, std::max<int64_t>(base_waves, 1)));
   ns = std::min(ns, 8);
@@ -120,15 +118,11 @@ Plan make_plan(const moe_layer_t* L, int T, int k) {
     p.n_split = nsd;
   }
   const int64_t hcols = Tk * L->d_ff + static_cast<int64_t>(S) * T * L->d_ff_shared;
-  // not used: part of the size, so that the workspace a caller has sized once,
-  // and the batches that fit the fixed no-allocation array, stay the same
-  p.reserved[0] = align256(sizeof(float) * static_cast<size_t>(rows) * (L->d_model / g));
-  p.reserved[1] = align256(sizeof(float) * static_cast<size_t>(rows) * (fmax / g));
   p.h_bytes = align256(sizeof(uint16_t) * static_cast<size_t>(hcols));
   p.tile_bytes = align256(sizeof(int32_t) * 2 * kTilePlanInts);
   const bool tiled = p.nt_routed == 0 || (S > 0 && p.nt_shared == 0);
   p.x16_bytes = tiled ? align256(sizeof(uint16_t) * static_cast<size_t>(T) * L->d_model) : 0;
-  p.total = p.reserved[0] + p.reserved[1] + p.h_bytes + p.tile_bytes + p.x16_bytes + 256;
+  p.total = p.h_bytes + p.tile_bytes + p.x16_bytes + 256;
   return p;
 }
 
@@ -385,8 +379,7 @@ int ffn_entry(const moe_layer_t* L, const uint16_t* x, int32_t T, int32_t k,
   {  // sizes of the buffer resources; every one must stay below 2^31 bytes
     const int64_t lim = int64_t{1} << 31;
     const int64_t xb = static_cast<int64_t>(T) * L->d_model * 2;
-    if (xb >= lim || static_cast<int64_t>(p.h_bytes) >= lim || static_cast<int64_t>(p.x16_bytes) >= lim ||
-        static_cast<int64_t>(p.reserved[0]) >= lim || static_cast<int64_t>(p.reserved[1]) >= lim)
+    if (xb >= lim || static_cast<int64_t>(p.h_bytes) >= lim || static_cast<int64_t>(p.x16_bytes) >= lim)
       return MOE_ERR_ARG;
     a.x16_bytes = static_cast<uint32_t>(p.x16_bytes);
     a.x_bytes = static_cast<uint32_t>(xb);

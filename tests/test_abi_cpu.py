@@ -184,6 +184,21 @@ def test_switch_and_ffn_validation(lib):
     assert na(C.byref(L), FAKE, 16, 2, FAKE, FAKE, FAKE, None, None) == -2
 
 
+@pytest.mark.parametrize("T,streams", [(1, True), (64, True), (600, False), (4096, False)])
+def test_ffn_workspace_holds_only_what_the_call_uses(lib, T, streams):
+    # the hidden activations, the tile kernel's two plans, its fp16 token copy
+    # where some experts take it, and the slack of the 256-byte alignment
+    L, keep = _fake_layer()
+    L.group, L.n_shared, L.d_ff_shared = 128, 0, 0
+    ns, wb = C.c_int32(0), C.c_size_t(0)
+    assert lib.moe_ffn_plan(C.byref(L), T, 2, C.byref(ns), C.byref(wb)) == 0
+    hidden, plans, copy = 2 * T * 2 * 512, 2 * 4 * 514, 0 if streams else 2 * T * 256
+
+    def up(n):
+        return (n + 255) // 256 * 256
+    assert wb.value == up(hidden) + up(plans) + up(copy) + 256
+
+
 def test_requant_validation(lib):
     L, keep = _fake_layer()
     rq = lib.moe_requant_channels
