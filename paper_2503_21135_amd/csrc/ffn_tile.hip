@@ -686,7 +686,7 @@ ffn_tile_kernel(FfnArgs a, TileMap map, const int32_t* __restrict__ plan, int32_
   // 470 / 456 at 4, 461 / 472 / 459 mixed; 4096 tokens 806 / 791 / 789, 842 / 833 /
   // 831, 756 / 754 / 750, 751 / 748 / 753 (the loss of L2 sharing: at equal lengths,
   // DeepSeek-shaped layer at 8192 tokens, it costs 1526 -> 1538).
-  const bool equal_k = NK == 2 || a.f == a.fs || map.n_e <= a.E;
+  const bool equal_k = NK == 2 || a.f == a.fs || map.e0 != 0 || map.n_e <= a.E;   // all routed or all shared
   const int n_fixed = equal_k ? max(total / G - 1, 0) : 0;
   for (int it = 0;; it++) {
     int item;
