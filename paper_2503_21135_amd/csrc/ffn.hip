@@ -352,7 +352,6 @@ int ffn_entry(const moe_layer_t* L, const uint16_t* x, int32_t T, int32_t k,
     const moe_kind_desc_t& kk = L->kind[kd];
     a.kd[kd] = KindDev{kk.codes, kk.sz, kk.code_off, kk.sz_off, kk.copy_codes, kk.copy_sz, kk.row_slot};
   }
-  a.bits = L->bits;
   a.order_gu = L->order_gu;
   a.order_dn = L->order_dn;
   a.class_cnt = L->class_cnt;
@@ -365,15 +364,12 @@ int ffn_entry(const moe_layer_t* L, const uint16_t* x, int32_t T, int32_t k,
   a.d = L->d_model;
   a.f = L->d_ff;
   a.fs = L->n_shared > 0 ? L->d_ff_shared : L->group * 2;
-  a.group = L->group;
   a.Tk = T * k;
-  a.rows = T * (k + L->n_shared);
   char* w = static_cast<char*>(ws);
   w = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(w) + 255) & ~static_cast<uintptr_t>(255));
   a.h = reinterpret_cast<uint16_t*>(w);
   a.tile_plan = reinterpret_cast<int32_t*>(w + p.h_bytes);
   a.x16 = reinterpret_cast<const uint16_t*>(w + p.h_bytes + p.tile_bytes);
-  a.n_split_out = p.n_split;
   a.o = o;
   a.split_stride = static_cast<int64_t>(T) * (k + L->n_shared) * L->d_model;
   {  // sizes of the buffer resources; every one must stay below 2^31 bytes

@@ -25,7 +25,6 @@ struct KindDev {
 
 struct FfnArgs {
   KindDev kd[3];
-  const int32_t* bits;
   const int32_t* order_gu;
   const int32_t* order_dn;
   const int32_t* class_cnt;
@@ -33,17 +32,15 @@ struct FfnArgs {
   const int32_t* offsets;
   const int32_t* perm;
   uint16_t* h;
-  float* o;
+  float* o;             // one slice per K slice of the down projection, which the combine adds
   int64_t split_stride;
-  int n_split_out;     // K slices of the down projection: slices of o the combine adds
   int32_t* tile_plan;   // workspace: 2 x kTilePlanInts, the tile kernel's plan of each stage
   const uint16_t* x16;  // [T][d] fp16 copy of x (tile kernel; row of permuted row p: perm[p])
   int32_t* status;      // device status word or null: MOE_ERR_RANGE when an fp16 operand overflows
   uint32_t x_bytes, h_bytes, x16_bytes;   // resource sizes (< 2^31)
   uint32_t copy_bytes[3], copy_sz_bytes[3];
-  int E, S, d, f, fs, group;
+  int E, S, d, f, fs;
   int Tk;    // routed rows T*k
-  int rows;  // all permuted rows T*(k+S)
 };
 
 // Row-offset of permuted row p in the h buffer (routed rows have d_ff
@@ -264,14 +261,14 @@ template <int NK, bool VEC>
 constexpr int kWavesOf = NK == 1 && !VEC ? 8 : 4;
 
 // Work map of one streaming launch.  Workgroups [0, n_r*n_sw*m_r) take the
-// switched classes of routed experts 0..n_r-1 (n_sw row blocks of one row
-// tile per wave per expert, m_r variants each); the rest are the class-0
+// switched classes of routed experts 0..n_r-1 (n_sw row blocks per
+// expert, m_r variants each); the rest are the class-0
 // row blocks of the entries: n_s shared experts with blk_s row blocks of
-// WV * 16 rows and m_s variants each, then the routed experts with blk_r
+// 16 rows per wave and m_s variants each, then the routed experts with blk_r
 // and m_r.  Equal blocks per entry make a workgroup's entry one division.
-// (Two or three row tiles per wave for narrow codes, so that every workgroup
-// streams about the same bytes, measured no faster: fewer, equal workgroups
-// leave a partial last round.)  A variant is a token-tile set (tt_r / tt_s
+// (32 or 48 rows per wave for narrow codes, so that every workgroup streams
+// about the same bytes, measured no faster: fewer, equal workgroups leave a
+// partial last round.)  A variant is a token-tile set (tt_r / tt_s
 // sets, each taking every n-th 32-token tile of the expert) and a K slice
 // (n_split).  Words of 32 bits throughout: a narrower element at a run-time
 // index is no scalar load.

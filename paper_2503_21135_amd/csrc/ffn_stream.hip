@@ -20,9 +20,9 @@
 // accumulation is the bf16 hidden activation h.
 //
 // Work decomposition (one wave = 64 lanes):
-//   - a wave owns 16*ROWT rows (neurons for gate/up, output channels for
-//     down) of one expert and streams its packed rows through all groups of
-//     K (down: one of n_split slices of K);
+//   - a wave owns 16 rows (neurons for gate/up, output channels for down) of
+//     one expert and streams its packed rows through all groups of K (down:
+//     one of n_split slices of K);
 //   - lane (r16 = lane % 16, kq = lane / 16) loads the group codes
 //     [kq*g/4, (kq+1)*g/4) of row r16 -- one 16-byte load at 4 bits -- and
 //     the matching activations of token r16 of the current 16-token tile;
@@ -35,14 +35,14 @@ namespace moe {
 namespace ffn {
 
 // ------------------------------------------------------------------ streaming kernel
-// One workgroup = kWavesOf<NK> waves on one expert and one source class of its rows.
-// Each wave owns 16*RT consecutive positions of the expert's row order for
+// One workgroup = kWavesOf<NK, VEC> waves on one expert and one source class of
+// its rows.  Each wave owns 16 consecutive positions of the expert's row order for
 // each of NK weight kinds (NK = 2: the gate and up rows of the same neurons;
 // NK = 1: down rows = output channels).  Within a class every kind has one
 // source for all rows -- the expert's base codes at bit-width B, or the
 // cached 8-bit copies -- so the loads are wave-uniform in shape and the code
 // registers are sized for that width (template BG / BU).  The packed codes of
-// the next kStages<RT, BG, BU> groups are in flight in registers while the current group
+// the next kStages<BG, BU> groups are in flight in registers while the current group
 // is dequantized and contracted; the activations of the workgroup's token
 // tile (NT*16 rows) are staged in LDS two groups at a time (double-buffered,
 // one barrier per two groups), so every wave reads them from LDS.
@@ -53,11 +53,8 @@ namespace ffn {
 // them (vector loads complete in order) never waits for a code load the loop
 // does not already need: with two-group chunks that holds for up to four
 // groups in flight.
-// With two or four row tiles per wave (narrow codes) two groups in flight
-// already hold as many bytes as four groups of one row tile.
-template <int RT, int BG, int BU>
-constexpr int kStages = (RT >= 2 || BG >= 8 || BU >= 8 || BG == 6 || BU == 6) ? 2 : 4;
-
+template <int BG, int BU>
+constexpr int kStages = (BG >= 8 || BU >= 8 || BG == 6 || BU == 6) ? 2 : 4;
 
 // Metadata a workgroup loads in its prologue, all issued before any is
 // waited for (a chain of dependent loads at the start of every workgroup
@@ -71,57 +68,49 @@ struct Pre {
 template <int NM, int B>
 constexpr int kWords = NM * B / 4;   // code words per lane per group
 
-template <int NM, int RT, int BG, int BU>
+template <int NM, int BG, int BU>
 struct Stage {
-  uint32_t cg[RT][(kWords<NM, BG>)];
-  uint32_t cu[RT][(kWords<NM, BU>)];   // unused for NK = 1
+  uint32_t cg[(kWords<NM, BG>)];
+  uint32_t cu[(kWords<NM, BU>)];   // unused for NK = 1
 };
 
 // Source of one kind for a workgroup: resources over the expert's codes and
 // {scale, zero} words (or the copies), the per-group stride of the {s, z}
 // words and the lane's byte offsets (kOOB for lanes past the rows of the
 // class).  The per-group advance goes into the scalar offset of the loads.
-template <int RT>
 struct Src {
   Rsrc code, sz;
-  uint32_t sz_gstride;     // bytes between consecutive groups' {s, z} words
-  uint32_t coff[RT];       // byte offset of the lane's code share of group 0
-  uint32_t soff[RT];       // byte offset of the row's {s, z} word of group 0
+  uint32_t sz_gstride;   // bytes between consecutive groups' {s, z} words
+  uint32_t coff;         // byte offset of the lane's code share of group 0
+  uint32_t soff;         // byte offset of the row's {s, z} word of group 0
 };
 
-template <int NM, int B, int RT>
-__device__ __forceinline__ void load_kind(uint32_t (&cw)[RT][(kWords<NM, B>)], const Src<RT>& s, int gi,
-                                          bool gv) {
+template <int NM, int B>
+__device__ __forceinline__ void load_kind(uint32_t (&cw)[(kWords<NM, B>)], const Src& s, int gi, bool gv) {
   constexpr uint32_t gcb = NM * 32 * B / 8;   // code bytes per row and group
   const uint32_t cadv = gv ? static_cast<uint32_t>(gi) * gcb : 0u;
-#pragma unroll
-  for (int rt = 0; rt < RT; rt++) bload<kWords<NM, B>>(cw[rt], s.code, gv ? s.coff[rt] : kOOB, cadv);
+  bload<kWords<NM, B>>(cw, s.code, gv ? s.coff : kOOB, cadv);
 }
 
 // {s, z} words of the four groups [gb, gb+4): lane (r16, kq) loads row r16's
-// word of group gb + kq (zero past g1), one load per kind and row tile for
-// four groups; each group then reads its word from lane r16 + 16*(g - gb).
-template <int RT, int NK>
-__device__ __forceinline__ void load_sz4(uint32_t (&szb)[RT][2], const Src<RT> (&src)[2], int gb, int g1,
-                                         int kq) {
+// word of group gb + kq (zero past g1), one load per kind for four groups; each
+// group then reads its word from lane r16 + 16*(g - gb).
+template <int NK>
+__device__ __forceinline__ void load_sz4(uint32_t (&szb)[2], const Src (&src)[2], int gb, int g1, int kq) {
   const bool ok = gb + kq < g1;
 #pragma unroll
   for (int kk = 0; kk < NK; kk++) {
     const uint32_t sadv = gb < g1 ? static_cast<uint32_t>(gb) * src[kk].sz_gstride : 0u;
-#pragma unroll
-    for (int rt = 0; rt < RT; rt++) {
-      const uint32_t so = src[kk].soff[rt];
-      const uint32_t voff = (ok && so != kOOB) ? so + static_cast<uint32_t>(kq) * src[kk].sz_gstride : kOOB;
-      szb[rt][kk] = __builtin_amdgcn_raw_buffer_load_b32(src[kk].sz, voff, sadv, 0);
-    }
+    const uint32_t so = src[kk].soff;
+    const uint32_t voff = (ok && so != kOOB) ? so + static_cast<uint32_t>(kq) * src[kk].sz_gstride : kOOB;
+    szb[kk] = __builtin_amdgcn_raw_buffer_load_b32(src[kk].sz, voff, sadv, 0);
   }
 }
 
-template <int NM, int RT, int NK, int BG, int BU>
-__device__ __forceinline__ void load_stage(Stage<NM, RT, BG, BU>& st, const Src<RT> (&src)[2], int gi,
-                                           bool gv) {
-  load_kind<NM, BG, RT>(st.cg, src[0], gi, gv);
-  if constexpr (NK == 2) load_kind<NM, BU, RT>(st.cu, src[1], gi, gv);
+template <int NM, int NK, int BG, int BU>
+__device__ __forceinline__ void load_stage(Stage<NM, BG, BU>& st, const Src (&src)[2], int gi, bool gv) {
+  load_kind<NM, BG>(st.cg, src[0], gi, gv);
+  if constexpr (NK == 2) load_kind<NM, BU>(st.cu, src[1], gi, gv);
 }
 
 // Contract one group: A fragments (activations) come from LDS.
@@ -152,39 +141,24 @@ __device__ __forceinline__ void contract_kind(const uint32_t (&cw)[(kWords<NM, B
   }
 }
 
-// The row tiles of a wave are contracted in turn, software-pipelined: the
-// MFMAs of row tile rt are issued before the scale/zero epilogue of tile
-// rt - 1, so the matrix cores work on one tile while the epilogue of the
-// previous one runs, and only two tiles' partial sums are live at once.
-template <int NM, int NT, int RT, int NK, int BG, int BU>
-__device__ __forceinline__ void compute_group(const Stage<NM, RT, BG, BU>& st, const uint32_t (&szw)[RT][2],
+template <int NM, int NT, int NK, int BG, int BU>
+__device__ __forceinline__ void compute_group(const Stage<NM, BG, BU>& st, const uint32_t (&szw)[2],
                                               const u32x4 (&af)[NT][NM], const f32x4 (&X)[NT],
-                                              uint32_t vm, uint32_t vh, f32x4 (&acc)[RT][NK][NT]) {
-  f32x4 tmp[2][NK][NT];
-  float sc[2][NK], zz[2][NK];
+                                              uint32_t vm, uint32_t vh, f32x4 (&acc)[NK][NT]) {
+  f32x4 tmp[NK][NT];
+  float sc[NK], zz[NK];
+  contract_kind<NM, NT, BG>(st.cg, szw[0], af, vm, vh, tmp[0], sc[0], zz[0]);
+  if constexpr (NK == 2) contract_kind<NM, NT, BU>(st.cu, szw[1], af, vm, vh, tmp[1], sc[1], zz[1]);
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int rt = 0; rt <= RT; rt++) {
-    if (rt < RT) {
-      const int b = rt & 1;
-      contract_kind<NM, NT, BG>(st.cg[rt], szw[rt][0], af, vm, vh, tmp[b][0], sc[b][0], zz[b][0]);
-      if constexpr (NK == 2)
-        contract_kind<NM, NT, BU>(st.cu[rt], szw[rt][1], af, vm, vh, tmp[b][1], sc[b][1], zz[b][1]);
-    }
-    if (rt > 0) {
-      const int b = (rt - 1) & 1;
-      __builtin_amdgcn_sched_barrier(0);
-      asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
-      __builtin_amdgcn_sched_barrier(0);
+  for (int kk = 0; kk < NK; kk++)
 #pragma unroll
-      for (int kk = 0; kk < NK; kk++)
+    for (int nt = 0; nt < NT; nt++)
 #pragma unroll
-        for (int nt = 0; nt < NT; nt++)
-#pragma unroll
-          for (int i = 0; i < 4; i++)
-            acc[rt - 1][kk][nt][i] = __fmaf_rn(sc[b][kk], __fmaf_rn(-zz[b][kk], X[nt][i], tmp[b][kk][nt][i]),
-                                               acc[rt - 1][kk][nt][i]);
-    }
-  }
+      for (int i = 0; i < 4; i++)
+        acc[kk][nt][i] = __fmaf_rn(sc[kk], __fmaf_rn(-zz[kk], X[nt][i], tmp[kk][nt][i]), acc[kk][nt][i]);
 }
 
 // Groups per LDS chunk of activations.  (Four-group chunks halve the
@@ -243,7 +217,7 @@ __device__ __forceinline__ float group_sum(const u32x4& v) {
 // The rows at order positions [pos0, pos1) of expert e (lanes past pos1
 // idle), class cls (bit kk set: kind kk reads the 8-bit copies), token tile
 // passes over the expert's segment, K groups [g0, g1) of split sp.
-template <int NM, int NT, int RT, int NK, int BG, int BU, int WV>
+template <int NM, int NT, int NK, int BG, int BU, int WV>
 __device__ __forceinline__ void stream_body(const FfnArgs& a, XTile<NM, NT>& tl, const Pre& pre, int e,
                                             int cls, int pos0, int pos1, int R, int sp, int n_split) {
   constexpr int kThreads = 64 * WV;
@@ -253,7 +227,7 @@ __device__ __forceinline__ void stream_body(const FfnArgs& a, XTile<NM, NT>& tl,
   constexpr int PIECES = TOK * KC / 8;   // 16-byte pieces per chunk
   constexpr int PPT = (PIECES + kThreads - 1) / kThreads;
   static_assert(PIECES % kThreads == 0 || PIECES < kThreads, "chunk must split evenly over the workgroup");
-  constexpr int S = kStages<RT, BG, BU>;
+  constexpr int S = kStages<BG, BU>;
   constexpr int CG = XTile<NM, NT>::CG;
   static_assert((S == 2 || S == 4) && CG == 2, "the loop body below handles two two-group chunks");
   static_assert(PPT <= g / 8, "one lane per piece writes a group sum");
@@ -274,23 +248,18 @@ __device__ __forceinline__ void stream_body(const FfnArgs& a, XTile<NM, NT>& tl,
   const int kind0 = down ? 2 : 0;
   const int32_t* order = down ? a.order_dn : a.order_gu;
 
-  int row_id[RT];
-  bool live[RT];
-#pragma unroll
-  for (int rt = 0; rt < RT; rt++) {
-    const int pos = pos0 + wv * 16 * RT + rt * 16 + r16;
-    live[rt] = pos < pos1;
-    // positions past the class (pos >= pos1) are not read: for the last
-    // expert's last class they would lie past the end of the order table
-    int prow = pre.row;
-    if (cls != 0) prow = live[rt] ? order[static_cast<int64_t>(e) * R + pos] : 0;
-    row_id[rt] = live[rt] ? prow : 0;
-  }
+  const int pos = pos0 + wv * 16 + r16;
+  const bool live = pos < pos1;
+  // positions past the class (pos >= pos1) are not read: for the last expert's
+  // last class they would lie past the end of the order table
+  int prow = pre.row;
+  if (cls != 0) prow = live ? order[static_cast<int64_t>(e) * R + pos] : 0;
+  const int row_id = live ? prow : 0;
   // a wave whose rows all lie past the class (the last workgroup of an
   // expert whose rows do not fill it) still stages activations and meets the
   // barriers, but contracts nothing
-  const bool wave_live = uni(pos0 + wv * 16 * RT) < pos1;
-  Src<RT> src[2];
+  const bool wave_live = uni(pos0 + wv * 16) < pos1;
+  Src src[2];
 #pragma unroll
   for (int kk = 0; kk < NK; kk++) {
     // scalar selects first, one resource each: a resource chosen by a branch
@@ -305,22 +274,18 @@ __device__ __forceinline__ void stream_body(const FfnArgs& a, XTile<NM, NT>& tl,
                             : static_cast<const void*>(kd.sz + uni(pre.sz_off[kk]));
     const uint32_t cbytes = copy ? a.copy_bytes[kind0 + kk] : static_cast<uint32_t>(R) * row_bytes;
     const uint32_t sbytes = copy ? a.copy_sz_bytes[kind0 + kk] : static_cast<uint32_t>(R) * G * 4u;
-    Src<RT>& s = src[kk];
+    Src& s = src[kk];
     s.code = make_rsrc(cptr, cbytes);
     s.sz = make_rsrc(sptr, sbytes);
     s.sz_gstride = copy ? 4u : static_cast<uint32_t>(R) * 4u;
-#pragma unroll
-    for (int rt = 0; rt < RT; rt++) {
-      const int slot = (copy && live[rt]) ? kd.row_slot[static_cast<int64_t>(e) * R + row_id[rt]] : -1;
-      const uint32_t c_base = live[rt] ? row_id[rt] * row_bytes + kq * words * 4u : kOOB;
-      const uint32_t s_base = live[rt] ? row_id[rt] * 4u : kOOB;
-      const uint32_t c_copy =
-          slot >= 0 ? static_cast<uint32_t>(slot) * 4u * static_cast<uint32_t>(code_row_words(K, 8)) + kq * (g / 4)
-                    : kOOB;
-      const uint32_t s_copy = slot >= 0 ? static_cast<uint32_t>(slot) * G * 4u : kOOB;
-      s.coff[rt] = copy ? c_copy : c_base;
-      s.soff[rt] = copy ? s_copy : s_base;
-    }
+    const int slot = (copy && live) ? kd.row_slot[static_cast<int64_t>(e) * R + row_id] : -1;
+    const uint32_t c_base = live ? row_id * row_bytes + kq * words * 4u : kOOB;
+    const uint32_t s_base = live ? row_id * 4u : kOOB;
+    const uint32_t c_copy =
+        slot >= 0 ? static_cast<uint32_t>(slot) * 4u * static_cast<uint32_t>(code_row_words(K, 8)) + kq * (g / 4) : kOOB;
+    const uint32_t s_copy = slot >= 0 ? static_cast<uint32_t>(slot) * G * 4u : kOOB;
+    s.coff = copy ? c_copy : c_base;
+    s.soff = copy ? s_copy : s_base;
   }
   const Rsrc xr = make_rsrc(down ? a.h : a.x, down ? a.h_bytes : a.x_bytes);
 
@@ -365,35 +330,31 @@ __device__ __forceinline__ void stream_body(const FfnArgs& a, XTile<NM, NT>& tl,
       if (xs_own) xs_dst[buf * (CG * TOK)] = sum;
     };
 
-    f32x4 acc[RT][NK][NT];
+    f32x4 acc[NK][NT];
 #pragma unroll
-    for (int rt = 0; rt < RT; rt++)
+    for (int kk = 0; kk < NK; kk++)
 #pragma unroll
-      for (int kk = 0; kk < NK; kk++)
-#pragma unroll
-        for (int nt = 0; nt < NT; nt++) acc[rt][kk][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int nt = 0; nt < NT; nt++) acc[kk][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // dequantization constants, kept in vector registers (see dequant_b)
     uint32_t vm = kMagic, vh = kHighMagic<BG, BU>;
     asm volatile("" : "+v"(vm), "+v"(vh));
-    Stage<NM, RT, BG, BU> st[S];
+    Stage<NM, BG, BU> st[S];
 #pragma unroll
-    for (int s = 0; s < S; s++) load_stage<NM, RT, NK, BG, BU>(st[s], src, g0 + s, g0 + s < g1);
+    for (int s = 0; s < S; s++) load_stage<NM, NK, BG, BU>(st[s], src, g0 + s, g0 + s < g1);
     u32x4 vx[CG == 2 ? 2 : 1][PPT];   // activations of the next chunk(s)
-    uint32_t szc[RT][2], szn[RT][2];   // {s, z} words of this and the next four groups
-    load_sz4<RT, NK>(szc, src, g0, g1, kq);
+    uint32_t szc[2], szn[2];   // {s, z} words of this and the next four groups
+    load_sz4<NK>(szc, src, g0, g1, kq);
     stage_x(vx[0], g0);
     write_x(vx[0], 0);
     if constexpr (CG == 2) stage_x(vx[1], g0 + 2);
     __syncthreads();
-    auto group = [&](Stage<NM, RT, BG, BU>& s, int buf, int gg, int gi, int i4) {
+    auto group = [&](Stage<NM, BG, BU>& s, int buf, int gg, int gi, int i4) {
       if (gi < g1 && wave_live) {   // wave-uniform; the loads below are unconditional
-        uint32_t szw[RT][2];
+        uint32_t szw[2];
 #pragma unroll
-        for (int rt = 0; rt < RT; rt++)
-#pragma unroll
-          for (int kk = 0; kk < NK; kk++)
-            szw[rt][kk] = static_cast<uint32_t>(__shfl(static_cast<int>(szc[rt][kk]), r16 + 16 * i4));
+        for (int kk = 0; kk < NK; kk++)
+          szw[kk] = static_cast<uint32_t>(__shfl(static_cast<int>(szc[kk]), r16 + 16 * i4));
         u32x4 af[NT][NM];
         f32x4 X[NT];
 #pragma unroll
@@ -403,9 +364,9 @@ __device__ __forceinline__ void stream_body(const FfnArgs& a, XTile<NM, NT>& tl,
             af[nt][m] = *reinterpret_cast<const u32x4*>(&tl.x[buf][nt * 16 + r16][gg * g + kq * (g / 4) + 8 * m]);
           X[nt] = *reinterpret_cast<const f32x4*>(&tl.xs[buf][gg][nt * 16 + 4 * kq]);
         }
-        compute_group<NM, NT, RT, NK, BG, BU>(s, szw, af, X, vm, vh, acc);
+        compute_group<NM, NT, NK, BG, BU>(s, szw, af, X, vm, vh, acc);
       }
-      load_stage<NM, RT, NK, BG, BU>(s, src, gi + S, gi + S < g1);
+      load_stage<NM, NK, BG, BU>(s, src, gi + S, gi + S < g1);
     };
     for (int gc = g0; gc < g1; gc += 4) {
 #pragma unroll
@@ -413,42 +374,36 @@ __device__ __forceinline__ void stream_body(const FfnArgs& a, XTile<NM, NT>& tl,
         // vx[c] held chunk gc+2c (written to LDS already); reuse it for gc+2c+4
         stage_x(vx[c], gc + 2 * c + 4);
         group(st[(2 * c) % S], c, 0, gc + 2 * c, 2 * c);
-        if (c == 0) load_sz4<RT, NK>(szn, src, gc + 4, g1, kq);
+        if (c == 0) load_sz4<NK>(szn, src, gc + 4, g1, kq);
         group(st[(2 * c + 1) % S], c, 1, gc + 2 * c + 1, 2 * c + 1);
         write_x(vx[c ^ 1], c ^ 1);   // chunk gc+2c+2, loaded one chunk ago
         __syncthreads();
       }
 #pragma unroll
-      for (int rt = 0; rt < RT; rt++)
-#pragma unroll
-        for (int kk = 0; kk < NK; kk++) szc[rt][kk] = szn[rt][kk];
+      for (int kk = 0; kk < NK; kk++) szc[kk] = szn[kk];
     }
 
     if constexpr (NK == 2) {
       // SiLU-GLU epilogue: h = bf16(silu(g) * u)
 #pragma unroll
-      for (int rt = 0; rt < RT; rt++)
+      for (int nt = 0; nt < NT; nt++)
 #pragma unroll
-        for (int nt = 0; nt < NT; nt++)
-#pragma unroll
-          for (int i = 0; i < 4; i++) {
-            const int p = t0 + nt * 16 + 4 * kq + i;
-            if (live[rt] && p < seg1) {
-              const float hv = silu_mul(acc[rt][0][nt][i], acc[rt][1][nt][i]);
-              a.h[h_row(a, p) + row_id[rt]] = static_cast<uint16_t>(bf16_rne(hv));
-            }
+        for (int i = 0; i < 4; i++) {
+          const int p = t0 + nt * 16 + 4 * kq + i;
+          if (live && p < seg1) {
+            const float hv = silu_mul(acc[0][nt][i], acc[1][nt][i]);
+            a.h[h_row(a, p) + row_id] = static_cast<uint16_t>(bf16_rne(hv));
           }
+        }
     } else {
       float* out = a.o + static_cast<int64_t>(sp) * a.split_stride;
 #pragma unroll
-      for (int rt = 0; rt < RT; rt++)
+      for (int nt = 0; nt < NT; nt++)
 #pragma unroll
-        for (int nt = 0; nt < NT; nt++)
-#pragma unroll
-          for (int i = 0; i < 4; i++) {
-            const int p = t0 + nt * 16 + 4 * kq + i;
-            if (live[rt] && p < seg1) out[static_cast<int64_t>(p) * R + row_id[rt]] = acc[rt][0][nt][i];
-          }
+        for (int i = 0; i < 4; i++) {
+          const int p = t0 + nt * 16 + 4 * kq + i;
+          if (live && p < seg1) out[static_cast<int64_t>(p) * R + row_id] = acc[0][nt][i];
+        }
     }
   }
 }
@@ -631,13 +586,13 @@ template <int NM, int NT, int NK, int B, int WV, bool VEC>
 __device__ __forceinline__ void dispatch_class(const FfnArgs& a, XTile<NM, NT>& tl, const Pre& pre, int e,
                                                int cls, int pos0, int pos1, int R, int sp, int n_split) {
   if constexpr (NK == 1) {
-    if (!VEC && cls == 0) stream_body<NM, NT, 1, 1, B, B, WV>(a, tl, pre, e, 0, pos0, pos1, R, sp, n_split);
-    else stream_body<NM, NT, 1, 1, 8, 8, WV>(a, tl, pre, e, 1, pos0, pos1, R, sp, n_split);
+    if (!VEC && cls == 0) stream_body<NM, NT, 1, B, B, WV>(a, tl, pre, e, 0, pos0, pos1, R, sp, n_split);
+    else stream_body<NM, NT, 1, 8, 8, WV>(a, tl, pre, e, 1, pos0, pos1, R, sp, n_split);
   } else {
-    if (!VEC && cls == 0) stream_body<NM, NT, 1, 2, B, B, WV>(a, tl, pre, e, 0, pos0, pos1, R, sp, n_split);
-    else if (cls == 1) stream_body<NM, NT, 1, 2, 8, B, WV>(a, tl, pre, e, 1, pos0, pos1, R, sp, n_split);
-    else if (cls == 2) stream_body<NM, NT, 1, 2, B, 8, WV>(a, tl, pre, e, 2, pos0, pos1, R, sp, n_split);
-    else stream_body<NM, NT, 1, 2, 8, 8, WV>(a, tl, pre, e, 3, pos0, pos1, R, sp, n_split);
+    if (!VEC && cls == 0) stream_body<NM, NT, 2, B, B, WV>(a, tl, pre, e, 0, pos0, pos1, R, sp, n_split);
+    else if (cls == 1) stream_body<NM, NT, 2, 8, B, WV>(a, tl, pre, e, 1, pos0, pos1, R, sp, n_split);
+    else if (cls == 2) stream_body<NM, NT, 2, B, 8, WV>(a, tl, pre, e, 2, pos0, pos1, R, sp, n_split);
+    else stream_body<NM, NT, 2, 8, 8, WV>(a, tl, pre, e, 3, pos0, pos1, R, sp, n_split);
   }
 }
 
@@ -665,7 +620,7 @@ __global__ void __launch_bounds__((64 * kWavesOf<NK, VEC>)) __attribute__((amdgp
 ffn_stream_kernel(FfnArgs a, WgMap map) {
   __shared__ __attribute__((aligned(16))) XTile<NM, NT> tl;
   constexpr int WV = kWavesOf<NK, VEC>;
-  constexpr int rows1 = WV * 16;   // rows of one row tile per wave
+  constexpr int rows1 = WV * 16;   // rows of the workgroup
   const int bid = blockIdx.x;
   const int n_swg = map.n_r * map.n_sw * map.m_r;
   int e, blk, v, B;
@@ -713,7 +668,6 @@ ffn_stream_kernel(FfnArgs a, WgMap map) {
   }
   if (uni(o1) <= uni(o0)) return;
   int cls = 0, start = 0, count = R;
-  constexpr int rows = rows1;
   if (routed) {
 #pragma unroll
     for (int c = 0; c < 4; c++) cnt[c] = uni(cnt[c]);
@@ -722,7 +676,7 @@ ffn_stream_kernel(FfnArgs a, WgMap map) {
       start = cnt[0];
       cls = 4;
       for (int c = 1; c < (NK == 1 ? 2 : 4); c++) {
-        const int nwg = (cnt[c] + rows - 1) / rows;
+        const int nwg = (cnt[c] + rows1 - 1) / rows1;
         if (blk < nwg) {
           cls = c;
           break;
@@ -734,9 +688,9 @@ ffn_stream_kernel(FfnArgs a, WgMap map) {
       count = cnt[cls];
     }
   }
-  const int pos0 = start + blk * rows;
-  if (blk * rows >= count) return;
-  const int pos1 = min(pos0 + rows, start + count);
+  const int pos0 = start + blk * rows1;
+  if (blk * rows1 >= count) return;
+  const int pos1 = min(pos0 + rows1, start + count);
   const int n_split = map.n_split;
   if constexpr (VEC) {
     if (cls == 0) {
