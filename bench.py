@@ -173,6 +173,10 @@ def ffn_source_hash():
     return h.hexdigest()[:16]
 
 
+# Spans between the five events of moe_expert_ffn_mixed_ev: the tile path's
+# preparation launch (a marker gap where every expert streams), the two stages
+# and the gap between them.
+STAGES = ("preparation", "gate_up", "between", "down")
 FFN_SOURCES = ("ffn.hip", "ffn_common.hpp", "ffn_stream.hip", "ffn_tile.hip", "common.hpp")
 
 
@@ -907,7 +911,7 @@ def main():
     sptr = stream.cuda_stream
     hip = HipEvents()
     K, W = args.steps, args.warmup
-    n_stage = 5                 # FFN stage boundaries: preparation | gate/up | (none) | down |
+    n_stage = len(STAGES) + 1   # FFN stage boundaries
     b = layer.buffers(wk.tokens)
 
     def step(evs=None):
@@ -974,8 +978,8 @@ def main():
     tokens_per_s = wk.tokens / (ms_per_step * 1e-3)
     log("ms/step %.4f (wall %.4f, host enqueue %.4f); gate/up launch %.4f ms" %
         (ms_per_step, wall / K * 1e3, enqueue / K * 1e3, gu_ms))
-    log("diagnostic pass stages ms: preparation %.4f gate/up %.4f between %.4f down %.4f; step %.4f" %
-        (*st, float(layer_ms.mean())))
+    log("diagnostic pass stages ms: %s; step %.4f" %
+        (" ".join("%s %.4f" % v for v in zip(STAGES, st)), float(layer_ms.mean())))
     log("gate/up %.1f GB/s %.1f TFLOP/s; FFN %.1f GB/s; %.2f TFLOP/s" %
         (achieved_gbs, achieved_tf, ffn_gbs, flops / (ffn_ms * 1e-3) / 1e12))
 
@@ -1055,7 +1059,7 @@ def main():
     hbm_bound = byt["gate_up"] / HBM_PEAK_GBS >= flops_gate_up(layer, offsets) / 1e3 / BF16_PEAK_TFLOPS
     kernel = ("FFN gate/up stage (gate+up projections, SiLU-GLU epilogue): ffn_stream_kernel "
               "for up to 28 tokens per expert (48 for experts narrower than d_ff 4096; shared "
-              "experts up to 512 tokens), else tile_prep_kernel + ffn_tile_kernel; routed and "
+              "experts up to 512 tokens), else ffn_tile_kernel; routed and "
               "shared experts in one launch per kernel")
     if hbm_bound:
         roof = {"bound": "hbm", "kernel": kernel, "achieved": round(achieved_gbs, 1),
@@ -1087,8 +1091,7 @@ def main():
             "diagnostic_step_ms": round(float(layer_ms.mean()), 5),
             "diagnostic_step_ms_p10_p50_p90": [round(float(np.percentile(layer_ms, q)), 5)
                                                for q in (10, 50, 90)],
-            "stage_ms": {"xsum": round(float(st[0]), 5), "gate_up": round(float(st[1]), 5),
-                         "hsum": round(float(st[2]), 5), "down": round(float(st[3]), 5)},
+            "stage_ms": {name: round(float(v), 5) for name, v in zip(STAGES, st)},
             "ffn_ms": round(ffn_ms, 5),
             "ffn_weight_bytes": int(byt["gate_up"] + byt["down"]),
             "ffn_gbs": round(ffn_gbs, 1), "ffn_hbm_frac": round(ffn_gbs / HBM_PEAK_GBS, 4),
