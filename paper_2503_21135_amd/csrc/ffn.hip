@@ -26,18 +26,28 @@ struct Plan {
   size_t h_bytes, tile_bytes, x16_bytes, total;
 };
 
+// The lines below: whole calls in us, streaming kernel / tile kernel, the rest of
+// the layer as the plan has it (repeated calls).  The streaming kernel's weights
+// are exact, the tile kernel's rounded to fp16, so a line does not move to the
+// tile kernel's side for speed alone.
+//
 // Shared experts with up to this many tokens stream, one workgroup set per
-// 32-token tile (measured on the Qwen-shaped layer, 512 tokens: step 440 ->
-// 389 us against the tile kernel's few items).
+// 32-token tile: the tile kernel has few items of them beside routed experts that
+// stream.  DeepSeek-shaped layer (1408 wide) 145 / 262 at 128 tokens, 290 / 366 at
+// 512; Qwen-shaped (5632 wide) 145 / 343, 289 / 422.  Once the routed experts take
+// the tile kernel too the shared ones fill its grid up: DeepSeek-shaped 309 / 248
+// at 640, Qwen-shaped 364 / 311 at 768.  Between (Qwen-shaped at 640, routed
+// experts still streaming) sets would be ahead, 334 / 450.
 constexpr int kSharedSplitMax = 512;
-// Routed experts expecting up to this many tokens stream too, with
-// workgroup sets taking every n_tt-th 32-token tile of the expert -- where the
-// experts are narrow (d_ff below kTileWideFf; DeepSeek-shaped layer, d_ff
-// 1408: the tile kernel is 13 % slower at 36 tokens per expert, even at 48,
-// 10-25 % faster from 56).  Wide experts give the tile kernel enough row
-// blocks to fill its grid at any token count, and there it is faster from 29
-// tokens per expert (Mixtral-shaped layer, 32 to 96 tokens per expert: FFN
-// 13-32 % faster).
+// Routed experts expecting up to this many tokens stream too, with workgroup sets
+// taking every n_tt-th 32-token tile of the expert, where they are narrow (d_ff
+// below kTileWideFf).  DeepSeek-shaped layer (d_ff 1408), shared experts
+// streaming: 220 / 230 at 28 tokens per expert, 249 / 258 at 36, 270 / 268 at 42,
+// 289 / 274 at 48; Qwen-shaped: 267 / 270 at 28, 290 / 287 at 34.  Beside shared
+// experts on the tile kernel: DeepSeek-shaped 396 / 242 at 56, Qwen-shaped 421 /
+// 281 at 36, 466 / 305 at 48.  Wide experts give the tile kernel enough row blocks
+// to fill its grid at any token count: Mixtral-shaped layer (d_ff 14336) 419 / 341
+// at 32, 453 / 376 at 48, 758 / 471 at 96.
 constexpr int kRoutedSplitMax = 48;
 constexpr int kTileWideFf = 4096;
 
@@ -65,7 +75,11 @@ constexpr int kTileSplitMinGroups = 8;
 // Streaming kernel for up to 28 expected tokens per expert (one or two
 // 16-token MFMA tiles, weights streamed once); beyond, make_plan spreads the
 // 32-token tiles of mid-sized experts over workgroup sets, and the rest go to
-// the tile kernel.
+// the tile kernel.  Mixtral-shaped layer, against the tile kernel: 233 / 315 at 8
+// tokens per expert, 259 / 322 at 16, 302 / 333 at 24, 348 / 336 at 28, 372 / 341
+// at 32.  One 16-token tile against two: 233 / 233 at 8, 258 / 242 at 12, 346 / 257
+// at 16 (experts past 16 tokens then stream their weights twice); DeepSeek-shaped
+// the same time up to 16.
 int pick_nt(double tokens) {
   if (tokens <= 12.0) return 1;
   if (tokens <= 28.0) return 2;

@@ -261,17 +261,19 @@ template <int NK, bool VEC>
 constexpr int kWavesOf = NK == 1 && !VEC ? 8 : 4;
 
 // Work map of one streaming launch.  Workgroups [0, n_r*n_sw*m_r) take the
-// switched classes of routed experts 0..n_r-1 (n_sw row blocks per
-// expert, m_r variants each); the rest are the class-0
-// row blocks of the entries: n_s shared experts with blk_s row blocks of
-// 16 rows per wave and m_s variants each, then the routed experts with blk_r
-// and m_r.  Equal blocks per entry make a workgroup's entry one division.
-// (32 or 48 rows per wave for narrow codes, so that every workgroup streams
-// about the same bytes, measured no faster: fewer, equal workgroups leave a
-// partial last round.)  A variant is a token-tile set (tt_r / tt_s
-// sets, each taking every n-th 32-token tile of the expert) and a K slice
-// (n_split).  Words of 32 bits throughout: a narrower element at a run-time
-// index is no scalar load.
+// switched classes of routed experts 0..n_r-1 (n_sw row blocks per expert, m_r
+// variants each); the rest are the class-0 row blocks of the entries: n_s shared
+// experts with blk_s row blocks of 16 rows per wave and m_s variants each, then
+// the routed experts with blk_r and m_r.  Equal blocks per entry make a
+// workgroup's entry one division.  (32 or 48 rows per wave for narrow codes, so
+// that every workgroup streams about the same bytes, measured no faster: fewer,
+// equal workgroups leave a partial last round.)  A variant is a token-tile set
+// (tt_r / tt_s sets, each taking every n-th 32-token tile of the expert) and a K
+// slice (n_split).  Words of 32 bits throughout: a narrower element at a run-time
+// index is no scalar load.  The host counts the copy headers of each expert for
+// n_sw in every call: 5 us at 10 to 13 thousand slots (tiny and Mixtral-shaped
+// layers), 13 at 29 thousand (Qwen-shaped), beside 13 us for the rest of the FFN's
+// host work.
 struct WgMap {
   int n_r, n_sw, m_r, m_s, tt_r, tt_s, n_split, n_s, blk_s, blk_r;
   int32_t ent[MOE_MAX_EXPERTS];            // entry i: expert, bit-width << 16

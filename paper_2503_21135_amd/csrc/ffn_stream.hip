@@ -421,12 +421,14 @@ __device__ __forceinline__ void stream_body(const FfnArgs& a, XTile<NM, NT>& tl,
 // in fp32 with the lane's activations; the lane applies its group's scale and
 // zero point to its own partial sum, and the lanes' sums are added at the end.
 // Eight rows' codes are in flight.
-// Measured, whole calls, against 16-token tiles: Mixtral-shaped 94.8 -> 76.6 us
-// at 1 token and 108.4 -> 105.7 at 2, DeepSeek-shaped 57.2 -> 47.3 and 61.4 ->
-// 56.7, Qwen-shaped 62.7 -> 51.8 and 70.4 -> 59.7.  With more tokens the launch
-// has waves enough and the matrix tile's fewer instructions per weight win:
-// chosen per expert by its token count it lost 2 to 13 % from 3 to 20 tokens on
-// the DeepSeek-shaped layer and up to 6 % from 6 on the Mixtral-shaped one.
+// Whole calls against 16-token tiles (repeated calls, weights partly in the
+// Infinity Cache): Mixtral-shaped 97.3 -> 79.7 us at 1 token and 108.9 -> 104.7 at
+// 2, DeepSeek-shaped 60.3 -> 50.0 and 63.1 -> 57.8, Qwen-shaped 66.2 -> 54.8 and
+// 72.4 -> 62.4.  With more tokens the launch has waves enough and the matrix tile's
+// fewer instructions per weight win: at 3 tokens 148.1 -> 140.6, 63.9 -> 66.5 and
+// 73.1 -> 77.8, at 4 148.1 -> 169.6, 69.6 -> 73.4 and 75.5 -> 83.0; chosen per
+// expert by its token count it lost 2 to 13 % from 3 to 20 tokens on the
+// DeepSeek-shaped layer and up to 6 % from 6 on the Mixtral-shaped one.
 
 // Sums of N values (a power of two, at most 64) over the wave: at each offset a
 // lane keeps half of its values and hands the other half over; value v ends in

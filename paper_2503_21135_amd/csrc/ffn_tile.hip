@@ -47,9 +47,9 @@ namespace ffn {
 // workgroup.  Work items (expert, row block, token tile; a down item also
 // takes a K slice and writes its own slice of o, which the combine adds) come
 // from a prefix table tile_prep_kernel builds from the routing offsets and
-// class counts, and are spread over a persistent grid so that the workgroups
-// of one XCD (hardware places workgroup b on XCD b % 8) take consecutive
-// items.  Within an expert the items run in super-tiles of kSuper row blocks
+// class counts, and are spread over a persistent grid: full rounds so that the
+// workgroups of one XCD (hardware places workgroup b on XCD b % 8) take consecutive
+// items, the last one to two rounds handed out one by one.  Within an expert the items run in super-tiles of kSuper row blocks
 // x kSuper token tiles, so that the workgroups one XCD runs together share
 // both their code rows and their activation rows through that XCD's L2.
 
@@ -622,7 +622,8 @@ __device__ __forceinline__ void tile_item(const FfnArgs& a, const TileLds& lds, 
 // kind j reads the 8-bit copies; down class 1 = copies.  The item's stage
 // count: the narrow widths' three stages where every wave of the item is of
 // class 0, else two.  The token tile of the item (an expert's last tile is
-// partial) picks one to four 32-token blocks.
+// partial) picks one to four 32-token blocks (three, which used to run as four:
+// Mixtral-shaped layer at 333 tokens, 83 per expert, 481 -> 445 us a call).
 template <int NM2, int NK, int B>
 __device__ __forceinline__ void tile_dispatch(const FfnArgs& a, const TileLds& lds, int e, int cls, bool base_item,
                                               int wpos, int wend, int R, int t0, int t1, int sp, int n_split) {
@@ -674,10 +675,11 @@ ffn_tile_kernel(FfnArgs a, TileMap map, const int32_t* __restrict__ plan, int32_
   // activation rows), all but the last; the rest are handed out one by one to
   // whichever workgroup is free: items of one kind differ by up to 2x in time
   // (partial row blocks, switched rows, HBM), and workgroups with a fixed share
-  // waited for the slowest one (with 96-token tiles and costly items first,
-  // fixed -> handed out: Mixtral-shaped layer at 333 tokens, 1.8 rounds, gate/up
-  // 279 -> 271 us, down 184 -> 177; at 4096 tokens, 15 rounds, the whole call
-  // 3.00 -> 2.86 ms).  Where the items contract different lengths of K (down, a
+  // waited for the slowest one.  Whole calls, fixed share -> handed out:
+  // Mixtral-shaped layer 362 -> 342 us at 128 tokens, 456 -> 445 at 333, 963 -> 968
+  // at 1024, 2916 -> 2865 at 4096; DeepSeek-shaped 262 -> 245 at 600, 1537 -> 1524
+  // at 8192.  (In index order instead of costly items first: 351, 444, 964, 2869;
+  // 247, 1527.)  Where the items contract different lengths of K (down, a
   // shared expert wider than the routed ones beside them) all are handed out,
   // the long ones first: a workgroup with a long item does not get a fixed share
   // of the short ones too.  Qwen-shaped layer (44 against 11 groups), whole calls
