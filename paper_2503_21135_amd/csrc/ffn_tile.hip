@@ -49,9 +49,10 @@ namespace ffn {
 // from a prefix table tile_prep_kernel builds from the routing offsets and
 // class counts, and are spread over a persistent grid: full rounds so that the
 // workgroups of one XCD (hardware places workgroup b on XCD b % 8) take consecutive
-// items, the last one to two rounds handed out one by one.  Within an expert the items run in super-tiles of kSuper row blocks
-// x kSuper token tiles, so that the workgroups one XCD runs together share
-// both their code rows and their activation rows through that XCD's L2.
+// items, the last one to two rounds handed out one by one.  Within an expert the
+// items run in super-tiles of kSuper row blocks x kSuper token tiles, so that the
+// workgroups one XCD runs together share both their code rows and their activation
+// rows through that XCD's L2.
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));

@@ -112,20 +112,20 @@ int pack_rows(int64_t n, int64_t K) {
   return rpw;
 }
 
-// The tiles go over a one-dimensional grid, row blocks innermost: its other
-// dimensions hold at most 65535 blocks, fewer than the widest rows have column
-// tiles.  A grid holds fewer than 2^32 threads.
-constexpr int64_t kPackMaxBlocks = (int64_t{1} << 24) - 1;
+// Grid of a launch over row blocks (x) and column tiles (y, then z): y and z
+// hold at most 65535 blocks each, fewer than the widest rows have column tiles,
+// and x fewer than 2^32 threads.
+constexpr int kPackGridY = 32768;
+constexpr int64_t kPackGridX = (int64_t{1} << 24) - 1;
 
-struct PackTile {
-  int row, col;   // row block, column tile
-};
-
-__device__ __forceinline__ PackTile pack_tile(int n, int rpw) {
-  const int row_blocks = (n - 1) / rpw + 1;
-  const int col = blockIdx.x / row_blocks;
-  return PackTile{static_cast<int>(blockIdx.x) - col * row_blocks, col};
+dim3 pack_grid(int64_t n, int rpw, int64_t K) {
+  const int64_t cols = cdiv(K, kPackCols);
+  return dim3(static_cast<unsigned>(cdiv(n, rpw)), static_cast<unsigned>(std::min<int64_t>(cols, kPackGridY)),
+              static_cast<unsigned>(cdiv(cols, kPackGridY)));
 }
+
+// Column tile of the workgroup; past the last one where the last z is not full.
+__device__ __forceinline__ int pack_col() { return blockIdx.y + kPackGridY * blockIdx.z; }
 
 // Quantize and pack rpw list rows x up to kPackCols columns per workgroup.
 // Bound by the fp32 reads.  The tile's 8-weight items run over the threads row
@@ -149,10 +149,10 @@ pack_kernel(const float* __restrict__ w, int64_t ld_w, int K, const int32_t* __r
   constexpr int qmax = (1 << (B & 15)) - 1;
   __shared__ uint32_t szl[kGroups][kPackRows];
   const int tid = threadIdx.x, lane = tid & 63;
-  const PackTile tile = pack_tile(n, rpw);
-  const int c0 = tile.col * kPackCols;
+  if (static_cast<int64_t>(pack_col()) * kPackCols >= K) return;
+  const int c0 = pack_col() * kPackCols;
   const int c8 = min(kPackCols, K - c0) / 8;   // items per row of the tile
-  const int i0 = tile.row * rpw;
+  const int i0 = blockIdx.x * rpw;
   const int nr = min(rpw, n - i0);
   auto load = [&](float (&v)[8], int it) {
     const bool on = it < nr * c8;   // the same for all lanes of a group
@@ -252,7 +252,7 @@ pack_kernel(const float* __restrict__ w, int64_t ld_w, int K, const int32_t* __r
   }
   __syncthreads();
   for (int t = tid; t < kGroups * kPackRows; t += 256) {
-    const int j = tile.col * kGroups + t / kPackRows, i = t % kPackRows;
+    const int j = pack_col() * kGroups + t / kPackRows, i = t % kPackRows;
     if (j < K / GR && i < nr) sz[static_cast<int64_t>(i0 + i) * sz_rs + static_cast<int64_t>(j) * sz_gs] = szl[t / kPackRows][i];
   }
 }
@@ -288,10 +288,10 @@ requant_kernel(const uint16_t* __restrict__ cache, int64_t ld_cache, int K,
   __shared__ uint32_t szl[kPackRows][kGroups];
   __shared__ int32_t bit_of[kPackRows];   // precision of each slot's expert, 0: left alone
   const int tid = threadIdx.x;
-  const PackTile tile = pack_tile(n_slots, rpw);
-  const int c0 = tile.col * kPackCols;
+  if (static_cast<int64_t>(pack_col()) * kPackCols >= K) return;
+  const int c0 = pack_col() * kPackCols;
   const int c8 = min(kPackCols, K - c0) / 8;   // items per row of the tile
-  const int s0 = tile.row * rpw;
+  const int s0 = blockIdx.x * rpw;
   const int ns = min(rpw, n_slots - s0);
   const int G = K / GR;
   if (tid < ns) bit_of[tid] = eb.b[hdr[2 * (s0 + tid)]];
@@ -349,7 +349,7 @@ requant_kernel(const uint16_t* __restrict__ cache, int64_t ld_cache, int K,
   }
   __syncthreads();
   for (int t = tid; t < kGroups * ns; t += 256) {
-    const int i = t / kGroups, j = tile.col * kGroups + t % kGroups;
+    const int i = t / kGroups, j = pack_col() * kGroups + t % kGroups;
     if (j < G && bit_of[i] != 0) sz[static_cast<int64_t>(s0 + i) * G + j] = szl[i][t % kGroups];
   }
 }
@@ -374,12 +374,12 @@ extern "C" int moe_quant_pack(const float* w, int64_t ld_w, int32_t R, int32_t K
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int rpw = pack_rows(n, K);
   auto launch = [&](auto kernel) {
-    const int64_t cols = cdiv(K, kPackCols), step = kPackMaxBlocks / cols * rpw;   // list rows of a launch
+    const int64_t step = kPackGridX * rpw;   // list rows of a launch
     for (int64_t i = 0; i < n; i += step) {
       const int m = static_cast<int>(std::min(step, n - i));
-      hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(cdiv(m, rpw) * cols)), dim3(256), 0, s,
-                         rows ? w : w + i * ld_w, ld_w, K, rows ? rows + i : rows, m, rpw, codes + i * ld_codes,
-                         ld_codes, sz + i * sz_row_stride, sz_row_stride, sz_group_stride, status);
+      hipLaunchKernelGGL(kernel, pack_grid(m, rpw, K), dim3(256), 0, s, rows ? w : w + i * ld_w, ld_w, K,
+                         rows ? rows + i : rows, m, rpw, codes + i * ld_codes, ld_codes, sz + i * sz_row_stride,
+                         sz_row_stride, sz_group_stride, status);
     }
   };
   if (group == 64) {
@@ -431,9 +431,9 @@ extern "C" int moe_requant_channels(moe_layer_t* L, int32_t kind, const uint16_t
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int rpw = pack_rows(D.n_slots, K);
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(cdiv(D.n_slots, rpw) * cdiv(K, kPackCols))), dim3(256), 0, s, cache, ld_cache, K, D.copy_hdr, D.n_slots, rpw, eb,
-                       const_cast<uint32_t*>(D.copy_codes), code_row_words(K, 8), const_cast<uint32_t*>(D.copy_sz),
-                       status);
+    hipLaunchKernelGGL(kernel, pack_grid(D.n_slots, rpw, K), dim3(256), 0, s, cache, ld_cache, K, D.copy_hdr,
+                       D.n_slots, rpw, eb, const_cast<uint32_t*>(D.copy_codes), code_row_words(K, 8),
+                       const_cast<uint32_t*>(D.copy_sz), status);
   };
   if (L->group == 64) launch(requant_kernel<64>);
   else launch(requant_kernel<128>);
