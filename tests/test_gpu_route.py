@@ -92,6 +92,24 @@ def test_route_misaligned_rows(orc, T):
     assert np.array_equal(g["w"].view(np.uint32), w.view(np.uint32))
 
 
+@pytest.mark.parametrize("E,k,S,misalign", [(1, 1, 0, False), (8, 8, 3, False), (15, 15, 2, False), (15, 4, 1, True),
+                                            (16, 2, 1, False), (20, 3, 1, True), (250, 16, 6, True)])
+@pytest.mark.parametrize("n_nan", [0, 1])
+def test_route_one_token(orc, E, k, S, misalign, n_nan):
+    # a single token's workgroup writes the permutation too: below 16 experts,
+    # and at any number of them where the token's row is off 16-byte alignment
+    rng = np.random.default_rng([E, k])
+    d = 192
+    x = mi.bf16_bits(rng.standard_normal((1, d)).astype(np.float32))
+    router = (rng.standard_normal((E, d)) * 0.02).astype(np.float32)
+    router[E - n_nan:] = np.nan
+    g = gpu_route(x, router, None, k, S, misalign=misalign)
+    _, ids, w = orc.route(x, router, k, None)
+    off, perm, inv = orc.permute(ids, E, S)
+    assert np.array_equal(g["ids"], ids) and np.array_equal(g["w"], w, equal_nan=True)
+    assert np.array_equal(g["off"], off) and np.array_equal(g["perm"], perm) and np.array_equal(g["inv"], inv)
+
+
 @pytest.mark.parametrize("T,E,k,n_nan", [(20, 8, 2, 1), (20, 8, 4, 6), (300, 8, 4, 6), (40, 20, 4, 18),
                                          (300, 20, 3, 2)])
 def test_route_nan_logits_rank_as_minus_inf(orc, T, E, k, n_nan):
