@@ -112,20 +112,21 @@ int pack_rows(int64_t n, int64_t K) {
   return rpw;
 }
 
-// Grid of a launch over row blocks (x) and column tiles (y, then z): y and z
-// hold at most 65535 blocks each, fewer than the widest rows have column tiles,
-// and x fewer than 2^32 threads.
-constexpr int kPackGridY = 32768;
+// A grid holds fewer than 2^32 threads along x (the row blocks) and 65536 blocks
+// along y (the column tiles): longer row lists and wider rows take several
+// launches.  launch(i, m, c, k): list rows [i, i + m), columns [c, c + k).
 constexpr int64_t kPackGridX = (int64_t{1} << 24) - 1;
+constexpr int64_t kPackGridY = 32768;
 
-dim3 pack_grid(int64_t n, int rpw, int64_t K) {
-  const int64_t cols = cdiv(K, kPackCols);
-  return dim3(static_cast<unsigned>(cdiv(n, rpw)), static_cast<unsigned>(std::min<int64_t>(cols, kPackGridY)),
-              static_cast<unsigned>(cdiv(cols, kPackGridY)));
+template <typename F>
+void pack_launches(int64_t n, int rpw, int64_t K, F launch) {
+  for (int64_t c = 0; c < K; c += kPackGridY * kPackCols)
+    for (int64_t i = 0; i < n; i += kPackGridX * rpw) {
+      const int m = static_cast<int>(std::min(n - i, kPackGridX * rpw));
+      const int k = static_cast<int>(std::min(K - c, kPackGridY * kPackCols));
+      launch(i, m, c, k, dim3(static_cast<unsigned>(cdiv(m, rpw)), static_cast<unsigned>(cdiv(k, kPackCols))));
+    }
 }
-
-// Column tile of the workgroup; past the last one where the last z is not full.
-__device__ __forceinline__ int pack_col() { return blockIdx.y + kPackGridY * blockIdx.z; }
 
 // Quantize and pack rpw list rows x up to kPackCols columns per workgroup.
 // Bound by the fp32 reads.  The tile's 8-weight items run over the threads row
@@ -149,8 +150,7 @@ pack_kernel(const float* __restrict__ w, int64_t ld_w, int K, const int32_t* __r
   constexpr int qmax = (1 << (B & 15)) - 1;
   __shared__ uint32_t szl[kGroups][kPackRows];
   const int tid = threadIdx.x, lane = tid & 63;
-  if (static_cast<int64_t>(pack_col()) * kPackCols >= K) return;
-  const int c0 = pack_col() * kPackCols;
+  const int c0 = blockIdx.y * kPackCols;
   const int c8 = min(kPackCols, K - c0) / 8;   // items per row of the tile
   const int i0 = blockIdx.x * rpw;
   const int nr = min(rpw, n - i0);
@@ -252,7 +252,7 @@ pack_kernel(const float* __restrict__ w, int64_t ld_w, int K, const int32_t* __r
   }
   __syncthreads();
   for (int t = tid; t < kGroups * kPackRows; t += 256) {
-    const int j = pack_col() * kGroups + t / kPackRows, i = t % kPackRows;
+    const int j = blockIdx.y * kGroups + t / kPackRows, i = t % kPackRows;
     if (j < K / GR && i < nr) sz[static_cast<int64_t>(i0 + i) * sz_rs + static_cast<int64_t>(j) * sz_gs] = szl[t / kPackRows][i];
   }
 }
@@ -281,19 +281,17 @@ template <int GR>
 __global__ void __launch_bounds__(256)
 requant_kernel(const uint16_t* __restrict__ cache, int64_t ld_cache, int K,
                const int32_t* __restrict__ hdr, int n_slots, int rpw, ExpertBits eb,
-               uint32_t* __restrict__ codes, int64_t ld_codes, uint32_t* __restrict__ sz,
+               uint32_t* __restrict__ codes, int64_t ld_codes, uint32_t* __restrict__ sz, int G,
                int32_t* status) {
   constexpr int kLanes = GR / 8;   // lanes of a group
   constexpr int kGroups = kPackCols / GR;
   __shared__ uint32_t szl[kPackRows][kGroups];
   __shared__ int32_t bit_of[kPackRows];   // precision of each slot's expert, 0: left alone
   const int tid = threadIdx.x;
-  if (static_cast<int64_t>(pack_col()) * kPackCols >= K) return;
-  const int c0 = pack_col() * kPackCols;
+  const int c0 = blockIdx.y * kPackCols;
   const int c8 = min(kPackCols, K - c0) / 8;   // items per row of the tile
   const int s0 = blockIdx.x * rpw;
   const int ns = min(rpw, n_slots - s0);
-  const int G = K / GR;
   if (tid < ns) bit_of[tid] = eb.b[hdr[2 * (s0 + tid)]];
   __syncthreads();
   // slot of an item: -1 past the tile and for slots left as they are (the
@@ -349,8 +347,8 @@ requant_kernel(const uint16_t* __restrict__ cache, int64_t ld_cache, int K,
   }
   __syncthreads();
   for (int t = tid; t < kGroups * ns; t += 256) {
-    const int i = t / kGroups, j = pack_col() * kGroups + t % kGroups;
-    if (j < G && bit_of[i] != 0) sz[static_cast<int64_t>(s0 + i) * G + j] = szl[i][t % kGroups];
+    const int i = t / kGroups, j = blockIdx.y * kGroups + t % kGroups;
+    if (j < K / GR && bit_of[i] != 0) sz[static_cast<int64_t>(s0 + i) * G + j] = szl[i][t % kGroups];
   }
 }
 
@@ -374,13 +372,11 @@ extern "C" int moe_quant_pack(const float* w, int64_t ld_w, int32_t R, int32_t K
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int rpw = pack_rows(n, K);
   auto launch = [&](auto kernel) {
-    const int64_t step = kPackGridX * rpw;   // list rows of a launch
-    for (int64_t i = 0; i < n; i += step) {
-      const int m = static_cast<int>(std::min(step, n - i));
-      hipLaunchKernelGGL(kernel, pack_grid(m, rpw, K), dim3(256), 0, s, rows ? w : w + i * ld_w, ld_w, K,
-                         rows ? rows + i : rows, m, rpw, codes + i * ld_codes, ld_codes, sz + i * sz_row_stride,
-                         sz_row_stride, sz_group_stride, status);
-    }
+    pack_launches(n, rpw, K, [&](int64_t i, int m, int64_t c, int k, dim3 grid) {
+      hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, (rows ? w : w + i * ld_w) + c, ld_w, k, rows ? rows + i : rows, m,
+                         rpw, codes + i * ld_codes + c * bits / 32, ld_codes,
+                         sz + i * sz_row_stride + c / group * sz_group_stride, sz_row_stride, sz_group_stride, status);
+    });
   };
   if (group == 64) {
     switch (bits) {
@@ -431,9 +427,11 @@ extern "C" int moe_requant_channels(moe_layer_t* L, int32_t kind, const uint16_t
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int rpw = pack_rows(D.n_slots, K);
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, pack_grid(D.n_slots, rpw, K), dim3(256), 0, s, cache, ld_cache, K, D.copy_hdr,
-                       D.n_slots, rpw, eb, const_cast<uint32_t*>(D.copy_codes), code_row_words(K, 8),
-                       const_cast<uint32_t*>(D.copy_sz), status);
+    pack_launches(D.n_slots, rpw, K, [&](int64_t i, int m, int64_t c, int k, dim3 grid) {
+      hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, cache + i * ld_cache + c, ld_cache, k, D.copy_hdr + 2 * i, m, rpw,
+                         eb, const_cast<uint32_t*>(D.copy_codes) + i * code_row_words(K, 8) + c / 4, code_row_words(K, 8),
+                         const_cast<uint32_t*>(D.copy_sz) + i * (K / L->group) + c / L->group, K / L->group, status);
+    });
   };
   if (L->group == 64) launch(requant_kernel<64>);
   else launch(requant_kernel<128>);
