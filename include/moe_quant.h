@@ -312,7 +312,9 @@ int moe_ffn_plan(const moe_layer_t* L, int32_t T, int32_t k,
  * that is >= 0 and the dequantized base codes otherwise.
  *
  *   x          device bf16 [T][d_model], original token order.
- *   offsets, perm_token   from moe_route_permute (T*k routed rows, S*T shared).
+ *   offsets, perm_token   from moe_route_permute (T*k routed rows, S*T shared), or
+ *              a caller's own: ascending segments of any sizes that add up to
+ *              these counts, tokens of a segment in any order and repeated.
  *   o          device fp32 [n_split][T*(k+S)][d_model]; the FFN output of row p
  *              is the sum over the n_split slices (moe_ffn_plan), which
  *              moe_unpermute_combine adds.  16-byte aligned.
